@@ -233,18 +233,17 @@ __device__ __forceinline__ bool meet_row(RowMeet m, int b, int c, int nchunks, u
 //
 // A row of V logits is split into `nchunks` chunks of `chunk_vec` 16-byte
 // vectors, one block of `threads` lanes each; with more than one chunk the
-// blocks meet in the workspace (above).  bf16 rows use 512-lane blocks, one
-// per row once B >= kStepOneBlockRows (a block per compute unit already) or
-// when B >= 64 and a row holds at most kStepSingleBlockRowBytes (a second
-// block per row buys nothing there); otherwise about 32 / sqrt(B) chunks per
-// row.  fp32 rows use 256-lane blocks and the same chunk rule.
+// blocks meet in the workspace (above).  Blocks have 512 lanes.  bf16 rows
+// take one per row once B >= kStepOneBlockRows (a block per compute unit
+// already) or when B >= 64 and a row holds at most kStepSingleBlockRowBytes
+// (a second block per row buys nothing there); otherwise, and for fp32 rows
+// always, about 32 / sqrt(B) chunks per row.
 constexpr int kStepOneBlockRows = 256;
-constexpr int kStepSmallThreads = 256;   // fp32 rows
-constexpr int kStepBigThreads = 512;     // bf16 rows
+constexpr int kStepThreads = 512;
 constexpr int kStepStageWords = 8192;    // mask words a bf16 block may stage in LDS
-constexpr int kStepMaxChunkVec = (kStepStageWords - 1) * 4 / kStepBigThreads * kStepBigThreads;
+constexpr int kStepMaxChunkVec = (kStepStageWords - 1) * 4 / kStepThreads * kStepThreads;
 constexpr int64_t kStepSingleBlockRowBytes = 65536;
-static_assert(kStepMaxChunkVec % kStepBigThreads == 0, "chunks are whole batches of lanes");
+static_assert(kStepMaxChunkVec % kStepThreads == 0, "chunks are whole batches of lanes");
 
 struct StepGeometry {
     int chunk_vec;
@@ -256,7 +255,7 @@ inline StepGeometry step_geometry(int B, int V, int dtype)
 {
     const bool bf16 = dtype == 1;
     const int vec = bf16 ? 8 : 4;  // elements per 16-byte vector
-    const int threads = bf16 ? kStepBigThreads : kStepSmallThreads;
+    const int threads = kStepThreads;
     const int nvec = V / vec;
     int want;
     if (bf16 && B >= kStepOneBlockRows) {

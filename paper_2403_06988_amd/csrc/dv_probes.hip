@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint32_t *__rest
 // aligned.
 constexpr int kFloorThreads = 512;
 constexpr int kFloorU = 2;
-static_assert(kFloorThreads == kStepBigThreads, "the step's block size");
+static_assert(kFloorThreads == kStepThreads, "the step's block size");
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 

@@ -4,7 +4,7 @@
 // The step reads B x V logits once: it is bound by HBM read bandwidth, so
 // the design is about keeping enough bytes in flight and spending few ALU
 // operations per element.
-//   * Launch shape (bf16, step_geometry).  A row is one 512-lane block once
+//   * Launch shape (step_geometry; bf16 figures).  A row is one 512-lane block once
 //     B >= 256 (every CU gets at least one row), or when B >= 64 and the row
 //     holds at most 32768 logits (a second block per row buys nothing
 //     there).  Otherwise each row is split into about 32 / sqrt(B) chunks,
@@ -49,9 +49,19 @@
 //   * A bf16 row need not be 16-byte aligned (any row stride): the elements
 //     before its first 16-byte boundary are read one by one and the mask
 //     bits of each vector are taken from two mask bytes, shifted.
-//   * fp32 rows (small workloads) use 256-lane blocks, the same head, vector
-//     and tail split (4 elements per vector) and exact keys with the
-//     index tracked per element.
+//   * fp32 rows take the same launch shapes and the same scan: 4 elements a
+//     vector, whose mask bits are half of a mask byte, and one 32-bit fast
+//     key per element, ANDed with its mask bit spread over the word (five
+//     VALU operations per element, well under the loads).  Chunks of 8 and
+//     more batches choose their loads two batches ahead at any number of
+//     blocks per unit; a 128-byte line is 32 tokens, so sparse masks leave
+//     more lines unread than in bf16.  An earlier form (256-lane blocks, 8
+//     cached loads per lane and then a per-element compare and select of key
+//     and index, no second batch in flight) read 1.5 TB/s.  us per step, 5 %
+//     of the tokens allowed, before and now: B = 256 x V = 128,256 83.0 and
+//     19.7 (131 MB of whole rows), 128 x 128,256 44.8 and 11.9 (13.6 with
+//     95 % allowed), 1,024 x 32,000 32.7 and 20.2, 64 x 128,256 24.9 and
+//     8.6, 8 x 32,000 6.5 and 5.0, 1 x 32,000 5.4 and 4.4.
 //   * Lanes combine (exact 32-bit key << 32 | ~index) as one 64-bit maximum:
 //     a larger key wins, on equal keys the smaller index wins.  The result
 //     does not depend on block or lane order, so the step is deterministic.
@@ -62,10 +72,8 @@
 namespace dv {
 namespace {
 
-constexpr int kSmallThreads = kStepSmallThreads;  // fp32 rows
-constexpr int kSmallU = 8;                         // 16-byte vectors per lane per batch
-constexpr int kBigThreads = kStepBigThreads;       // lanes per bf16 block
-constexpr int kBigU = 2;                           // vectors per lane per batch (x2: double-buffered)
+constexpr int kThreads = kStepThreads;  // lanes per block
+constexpr int kU = 2;                    // 16-byte vectors per lane per batch (x2: double-buffered)
 
 // Order-preserving key of an fp32 bit pattern under the step's value rules:
 // NaN ranks as -inf and -0.0 equals +0.0.  Every real value's key is
@@ -92,28 +100,25 @@ __device__ __forceinline__ uint32_t fast_key2(uint32_t w)
     return w ^ (__builtin_bit_cast(uint32_t, sign) | 0x80008000u);
 }
 
+// The same of one fp32 value.  Exact except: -0.0 -> 0x7FFFFFFF, positive NaN
+// -> (0xFF800000, 0xFFFFFFFF], negative NaN -> [0, 0x007FFFFF).
+__device__ __forceinline__ uint32_t fast_key(uint32_t x)
+{
+    return x ^ ((uint32_t)((int32_t)x >> 31) | 0x80000000u);
+}
+
+// All ones where bit e of m is set, else 0.
+__device__ __forceinline__ uint32_t lane_mask(uint32_t m, uint32_t e)
+{
+    return (uint32_t)__builtin_amdgcn_sbfe((int)m, e, 1u);
+}
+
 __device__ __forceinline__ uint64_t pack(uint32_t key, int idx)
 {
     return key ? ((uint64_t)key << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)idx) : 0ull;
 }
 
 __device__ __forceinline__ uint64_t wave_max(uint64_t v) { return wave_reduce<true>(v); }
-
-template <int THREADS>
-__device__ __forceinline__ uint64_t block_max(uint64_t v)
-{
-    __shared__ uint64_t red[THREADS / kWave];
-    v = wave_max(v);
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (lane == 0)
-        red[wave] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < THREADS / kWave; ++w)
-            v = red[w] > v ? red[w] : v;
-    }
-    return v;  // valid in thread 0
-}
 
 // "next state not loaded yet": the winner was not a vector-path best.
 constexpr int kNsUnknown = INT_MIN;
@@ -175,12 +180,14 @@ __device__ __forceinline__ uint64_t block_max_ns(uint64_t v, uint64_t vec_pack, 
 
 template <int DT> struct Elt;
 template <> struct Elt<0> {  // fp32
+    static constexpr int kBytes = 4, kVec = 4;  // bytes of an element, elements of a 16-byte vector
     __device__ static uint32_t bits(const char *row, int64_t i)
     {
         return reinterpret_cast<const uint32_t *>(row)[i];
     }
 };
 template <> struct Elt<1> {  // bf16: the high half of an fp32
+    static constexpr int kBytes = 2, kVec = 8;
     __device__ static uint32_t bits(const char *row, int64_t i)
     {
         return (uint32_t)reinterpret_cast<const uint16_t *>(row)[i] << 16;
@@ -204,97 +211,6 @@ __device__ __forceinline__ void scan_exact(const char *row, const uint32_t *arow
     }
 }
 
-// fp32 rows are read as a head of `head` < 4 elements (up to the row's first
-// 16-byte boundary), 16-byte vectors from element `head` on, and a tail of
-// fewer than 4 elements.  Vector v holds elements i = head + 4v .. i + 3,
-// whose mask bits straddle two mask words when i mod 32 > 28.
-__device__ __forceinline__ int f32_head(const char *row, int V)
-{
-    return min(V, (int)(((16u - (uint32_t)(reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) >> 2));
-}
-
-// Vector path over vectors [v0, v1) past the head; each lane takes U vectors
-// per batch, strided by THREADS so loads coalesce.  Per lane, elements are
-// visited in increasing index order and only a strictly larger key replaces
-// the lane's best, so the lane keeps the lowest index of its maximum.
-template <int THREADS, int U>
-__device__ __forceinline__ void scan_vectors_f32(const char *row, const uint32_t *arow, int head, int v0, int v1,
-                                                 uint32_t &best_key, int &best_idx)
-{
-    const char *vrow = row + 4 * head;  // 16-byte aligned
-    const int tid = threadIdx.x;
-    for (int vb = v0; vb < v1; vb += THREADS * U) {
-        uint4 d[U];
-        uint32_t m[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int v = vb + u * THREADS + tid;
-            if (v < v1) {
-                d[u] = *reinterpret_cast<const uint4 *>(vrow + (size_t)v * 16);
-                const int i = head + 4 * v, w = i >> 5, sh = i & 31;
-                uint32_t bits = arow[w] >> sh;
-                if (sh > 28)  // element i + 3 < V, so word w + 1 is in the row
-                    bits |= arow[w + 1] << (32 - sh);
-                m[u] = bits & 0xFu;
-            } else {
-                d[u] = make_uint4(0, 0, 0, 0);
-                m[u] = 0;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = head + 4 * (vb + u * THREADS + tid);
-            const uint32_t w[4] = {d[u].x, d[u].y, d[u].z, d[u].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t key = ((m[u] >> e) & 1u) ? f32_key(w[e]) : 0u;
-                if (key > best_key) {
-                    best_key = key;
-                    best_idx = i + e;
-                }
-            }
-        }
-    }
-}
-
-// fp32 rows, 256-lane blocks, exact keys.
-template <int THREADS, int U>
-__global__ __launch_bounds__(THREADS) void masked_step_kernel(
-    const int32_t *__restrict__ next_state, const uint32_t *__restrict__ allow, int S, int V, int W,
-    const int32_t *__restrict__ states, const void *__restrict__ logits, RowMap map, int chunk_vec,
-    int nchunks, int32_t *__restrict__ token, int32_t *__restrict__ new_state, RowMeet meet)
-{
-    const int b = blockIdx.x / nchunks;
-    const int c = blockIdx.x - b * nchunks;
-    const int s = row_state(states, map, next_state, allow, S, V, b);
-    const bool live = (uint32_t)s < (uint32_t)S;
-
-    uint32_t best_key = 0;
-    int best_idx = 0;
-    if (live) {
-        const char *row = static_cast<const char *>(logits) + (size_t)map.offset(b) * 4;
-        const uint32_t *arow = allow + (size_t)s * W;
-        const int head = f32_head(row, V);
-        const int nvec = (V - head) / 4;
-        // increasing index order per lane: head, vectors, tail
-        if (c == 0)
-            scan_exact<0, THREADS>(row, arow, 0, head, best_key, best_idx);
-        scan_vectors_f32<THREADS, U>(row, arow, head, c * chunk_vec, min(nvec, (c + 1) * chunk_vec), best_key,
-                                     best_idx);
-        if (c == nchunks - 1)
-            scan_exact<0, THREADS>(row, arow, head + nvec * 4, V, best_key, best_idx);
-    }
-    uint64_t best = block_max<THREADS>(pack(best_key, best_idx));
-    if (threadIdx.x != 0)
-        return;
-    if (nchunks > 1 && !meet_row(meet, b, c, nchunks, best, best))
-        return;  // another block of the row finishes it
-    const int tok = best ? (int)(0xFFFFFFFFu - (uint32_t)best) : -1;
-    const bool found = tok >= 0 && tok < V;  // always true for a found token; guards the read
-    token[b] = found ? tok : -1;
-    new_state[b] = found ? next_state[(size_t)s * V + tok] : -1;
-}
-
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b)
@@ -308,7 +224,8 @@ __device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t v, bool is_max)
     return is_max ? wave_reduce<true>(v) : wave_reduce<false>(v);  // in every lane of the wave
 }
 
-// bf16 rows.  Per batch of U vectors per lane:
+// Rows of either type.  Per batch of U vectors per lane (bf16 described;
+// an fp32 vector's keys are 32-bit, masked by their mask bits):
 //   pass 1: packed 16-bit fast keys, masked through an LDS table that turns
 //           a mask byte into four 32-bit lane masks, folded with
 //           v_pk_max_u16 -- two VALU operations per logit;
@@ -352,7 +269,7 @@ __device__ __forceinline__ void fill_lut(uint4 *lut)
 // branch makes the compiler wait for every outstanding load at the join,
 // which would serialise the double buffer.)
 template <int THREADS, int U>
-__device__ __forceinline__ void load_batch_bf16(uint4 (&d)[U], const char *row, int vb, int v1)
+__device__ __forceinline__ void load_batch(uint4 (&d)[U], const char *row, int vb, int v1)
 {
     const int tid = threadIdx.x;
 #pragma unroll
@@ -400,29 +317,42 @@ __device__ __forceinline__ void load_batch_buf_sel(uint4 (&d)[U], __amdgpu_buffe
     }
 }
 
-template <int THREADS, int U>
+// The mask bytes of aligned vectors: one per bf16 vector, one per two fp32
+// vectors.
+template <int DT>
+__device__ __forceinline__ uint32_t mask_bytes(int nvec)
+{
+    return DT == 1 ? (uint32_t)nvec : (uint32_t)(nvec + 1) >> 1;
+}
+
+template <int DT, int THREADS, int U>
 __device__ __forceinline__ void load_masks_buf(uint32_t (&m)[U], __amdgpu_buffer_rsrc_t r, int vb)
 {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-        m[u] = __builtin_amdgcn_raw_buffer_load_b8(r, vb + u * THREADS + (int)threadIdx.x, 0, 0);
+    for (int u = 0; u < U; ++u) {
+        const int v = vb + u * THREADS + (int)threadIdx.x;
+        m[u] = __builtin_amdgcn_raw_buffer_load_b8(r, DT == 1 ? v : v >> 1, 0, 0);
+    }
 }
 
-// A row is read as a head of `head` < 8 elements (its first 16-byte
+// A bf16 row is read as a head of `head` < 8 elements (its first 16-byte
 // boundary), then 16-byte vectors from element `head` on, then a tail of
 // fewer than 8 elements.  Vector v holds elements head + 8v .. head + 8v + 7,
 // whose mask bits are bits head .. head + 7 of allow bytes v and v + 1 (just
-// byte v when head = 0).  Rows of any alignment (any row stride) thus take
+// byte v when head = 0).  An fp32 row is split alike, by 4 elements: vector
+// v's mask bits are bits head + 4v .. head + 4v + 3 of the allow row.  Rows of any alignment (any row stride) thus take
 // the vector path; the head and the tail are scanned element by element.
 struct RowSplit {
-    int head;  // elements before the first 16-byte boundary (< 8)
+    int head;  // elements before the first 16-byte boundary (fewer than a vector holds)
     int nvec;  // 16-byte vectors after the head
 };
 
+template <int DT>
 __device__ __forceinline__ RowSplit split_row(const char *row, int V)
 {
-    const int head = min(V, (int)(((16u - (uint32_t)(reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) >> 1));
-    return {head, (V - head) / 8};
+    const int head =
+        min(V, (int)(((16u - (uint32_t)(reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) / (unsigned)Elt<DT>::kBytes));
+    return {head, (V - head) / Elt<DT>::kVec};
 }
 
 // This lane's packed best (exact key << 32 | ~index, 0 if none) over the
@@ -441,19 +371,21 @@ __device__ __forceinline__ RowSplit split_row(const char *row, int V)
 // load_batch_buf_sel).  AHEAD2 (aligned rows streamed from memory): the
 // mask bytes are read two batches ahead of their logits and choose the
 // loads in the same way.
-template <int THREADS, int U, bool MASKED, bool SHIFTED, bool STAGED, bool SELECT, bool AHEAD2 = false>
-__device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *arow, const uint8_t *mbytes,
+template <int DT, int THREADS, int U, bool MASKED, bool SHIFTED, bool STAGED, bool SELECT, bool AHEAD2 = false>
+__device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *arow, const uint8_t *mbytes,
                                               int moff, const int32_t *ns_row, RowSplit rs, int v0, int v1,
                                               bool first, bool last, int V, const uint4 *lut, uint4 (&da)[U],
                                               uint4 (&db)[U], uint64_t &vec_pack, int &vec_ns)
 {
     static_assert(!SELECT || STAGED, "selection reads the staged mask bytes");
     static_assert(!AHEAD2 || (MASKED && !STAGED), "two batches ahead: the streamed mask bytes choose the loads");
-    constexpr int kVec = 8;
+    static_assert(DT == 1 || !STAGED, "the staged mask bytes hold one byte per bf16 vector");
+    constexpr int kVec = Elt<DT>::kVec;
     constexpr int kStep = THREADS * U;  // vectors per batch
+    static_assert(THREADS % 2 == 0, "an fp32 vector's half of its mask byte is the lane's parity");
     const int tid = threadIdx.x;
     const int head = SHIFTED ? rs.head : 0;
-    const char *vrow = row + 2 * head;  // 16-byte aligned
+    const char *vrow = row + Elt<DT>::kBytes * head;  // 16-byte aligned
     uint32_t best_key = 0;  // exact key of the wave's best vector-path element, wave-uniform
     int best_idx = 0;
     int best_ns = kNsUnknown;
@@ -464,6 +396,12 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
         auto mask_of = [&](int v) -> uint32_t {
             if constexpr (!MASKED) {
                 return 0xFFu;
+            } else if constexpr (DT == 0) {
+                const int i = head + kVec * v, w = i >> 5, sh = i & 31;
+                uint32_t bits = arow[w] >> sh;
+                if (SHIFTED && sh > 28)  // element i + 3 < V, so word w + 1 is in the row
+                    bits |= arow[w + 1] << (32 - sh);
+                return bits & 0xFu;
             } else if constexpr (!SHIFTED) {
                 return mbytes[v - moff];
             } else {
@@ -487,9 +425,16 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
         // for every earlier one), so while a batch is reduced the next is in
         // flight.
         //
+        // The mask bits of a streamed batch as the buffer loads bring them: a
+        // bf16 vector's own byte, or the byte that an fp32 vector shares with
+        // its neighbour, whose half is the lane's parity (a batch starts at
+        // an even vector).
+        const uint32_t half = (uint32_t)(tid & 1) * 4u;
+        auto bits_of = [&](uint32_t m) { return DT == 1 ? m : __builtin_amdgcn_ubfe(m, half, 4u); };
         // Mask bytes with the lanes past the chunk zeroed (the buffer loads
-        // of the aligned streaming scans already read zeros there).
-        constexpr bool kZeroPast = MASKED && !SHIFTED && !STAGED;
+        // of the aligned streaming bf16 scans already read zeros there; an
+        // fp32 chunk's last byte may hold bits of the vector past its end).
+        constexpr bool kZeroPast = DT == 1 && MASKED && !SHIFTED && !STAGED;
         auto live = [&](uint32_t (&m)[U], int vb) {
             if constexpr (!kZeroPast) {
 #pragma unroll
@@ -497,17 +442,35 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
                     m[u] = vb + u * THREADS + tid < v1 ? m[u] : 0u;
             }
         };
-        // mask-table entries of live mask bytes: two 16-bit lane masks per word
+        // mask-table entries of live mask bytes: two 16-bit lane masks per
+        // word (fp32 keys are masked by the mask bits themselves)
         auto entries = [&](uint4 (&l)[U], const uint32_t (&m)[U]) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if constexpr (MASKED) {
+                if constexpr (DT == 0) {
+                    l[u] = make_uint4(0, 0, 0, 0);
+                } else if constexpr (MASKED) {
                     l[u] = lut[m[u]];
                 } else {
                     const uint32_t all = m[u] ? 0xFFFFFFFFu : 0u;
                     l[u] = make_uint4(all, all, all, all);
                 }
             }
+        };
+        // a streamed batch's own mask bits, in place (nothing to do for bf16)
+        auto own = [&](uint32_t (&m)[U], int vb) {
+            if constexpr (DT == 0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    m[u] = bits_of(m[u]);
+                live(m, vb);
+            }
+        };
+        // which vectors of a batch are needed (its mask bits still as loaded)
+        auto choose = [&](uint32_t (&sel)[U], const uint32_t (&m)[U]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                sel[u] = bits_of(m[u]);
         };
         // masked keys of a batch; returns whether the lane has an allowed
         // element in it
@@ -517,10 +480,17 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 any |= m[u];
-                km[4 * u + 0] = fast_key2(d[u].x) & l[u].x;
-                km[4 * u + 1] = fast_key2(d[u].y) & l[u].y;
-                km[4 * u + 2] = fast_key2(d[u].z) & l[u].z;
-                km[4 * u + 3] = fast_key2(d[u].w) & l[u].w;
+                if constexpr (DT == 1) {
+                    km[4 * u + 0] = fast_key2(d[u].x) & l[u].x;
+                    km[4 * u + 1] = fast_key2(d[u].y) & l[u].y;
+                    km[4 * u + 2] = fast_key2(d[u].z) & l[u].z;
+                    km[4 * u + 3] = fast_key2(d[u].w) & l[u].w;
+                } else {
+                    km[4 * u + 0] = fast_key(d[u].x) & lane_mask(m[u], 0);
+                    km[4 * u + 1] = fast_key(d[u].y) & lane_mask(m[u], 1);
+                    km[4 * u + 2] = fast_key(d[u].z) & lane_mask(m[u], 2);
+                    km[4 * u + 3] = fast_key(d[u].w) & lane_mask(m[u], 3);
+                }
             }
             return any;
         };
@@ -532,30 +502,46 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
             uint32_t acc = 0;
 #pragma unroll
             for (int i = 0; i < 4 * U; ++i)
-                acc = pk_max_u16(acc, km[i]);
-            const uint32_t lane_max = max(acc & 0xFFFFu, acc >> 16);
-            const uint32_t top = wave_reduce_u32((lane_max << 1) | (any ? 1u : 0u), true);
-            const uint32_t k16 = top >> 1;
-            if (k16 == 0 && (top & 1u) == 0)
-                return;  // nothing allowed in this batch
-            const bool special = k16 <= 0x007Fu || k16 == 0x7FFFu || k16 == 0x8000u || k16 > 0xFF80u;
+                acc = DT == 1 ? pk_max_u16(acc, km[i]) : max(acc, km[i]);
+            uint32_t lane_max = acc, top;
+            bool special;
+            if constexpr (DT == 1) {
+                lane_max = max(acc & 0xFFFFu, acc >> 16);
+                const uint32_t t = wave_reduce_u32((lane_max << 1) | (any ? 1u : 0u), true);
+                top = t >> 1;
+                if (t == 0)
+                    return;  // nothing allowed in this batch
+                special = top <= 0x007Fu || top == 0x7FFFu || top == 0x8000u || top > 0xFF80u;
+            } else {
+                top = wave_reduce_u32(acc, true);
+                if (top == 0 && !__any(any))
+                    return;
+                special = top <= 0x007FFFFFu || top == 0x7FFFFFFFu || top == 0x80000000u || top > 0xFF800000u;
+            }
             if (!special) {
-                const uint32_t h = (k16 & 0x8000u) ? (k16 & 0x7FFFu) : (~k16 & 0xFFFFu);
-                const uint32_t key = f32_key(h << 16);
+                uint32_t key = top;  // an fp32 value's fast key is its exact one
+                if constexpr (DT == 1) {
+                    const uint32_t h = (top & 0x8000u) ? (top & 0x7FFFu) : (~top & 0xFFFFu);
+                    key = f32_key(h << 16);
+                }
                 if (key <= best_key)
                     return;  // an earlier batch of this wave (lower indices) is at least as good
-                // first allowed element whose bits are h: a non-special k16
-                // is not 0, and the fast key is one-to-one, so a masked key
-                // equal to k16 is exactly that
+                // first allowed element of that key: a non-special top is not
+                // 0, and the fast key is one-to-one, so a masked key equal to
+                // it is exactly that value, allowed
                 int pos = 0x7FFFFFFF;
-                if (lane_max == k16) {
+                if (lane_max == top) {
 #pragma unroll
                     for (int i = 4 * U - 1; i >= 0; --i) {
-                        const int e = head + (vb + (i / 4) * THREADS + tid) * kVec + 2 * (i % 4);
-                        if ((km[i] >> 16) == k16)
-                            pos = e + 1;
-                        if ((km[i] & 0xFFFFu) == k16)
+                        const int e = head + (vb + (i / 4) * THREADS + tid) * kVec + (kVec / 4) * (i % 4);
+                        if constexpr (DT == 1) {
+                            if ((km[i] >> 16) == top)
+                                pos = e + 1;
+                            if ((km[i] & 0xFFFFu) == top)
+                                pos = e;
+                        } else if (km[i] == top) {
                             pos = e;
+                        }
                     }
                 }
                 best_idx = (int)wave_reduce_u32((uint32_t)pos, false);
@@ -574,7 +560,7 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
                     for (int e = 0; e < kVec; ++e) {
                         if ((mb >> e) & 1u) {
                             const int i = head + v * kVec + e;
-                            const uint32_t key = f32_key(Elt<1>::bits(row, i));
+                            const uint32_t key = f32_key(Elt<DT>::bits(row, i));
                             if (key > bk) {
                                 bk = key;
                                 bi = i;
@@ -602,7 +588,7 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
                 if constexpr (SELECT && MASKED && !SHIFTED)
                     load_batch_buf_sel<THREADS, U>(d, rl, vb, sel);
                 else
-                    load_batch_bf16<THREADS, U>(d, vrow, vb, v1);
+                    load_batch<THREADS, U>(d, vrow, vb, v1);
             };
             uint32_t na[U], nb[U];
             load_masks(ma, v0);
@@ -649,12 +635,13 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
             // Mask bytes one batch ahead, each issued before its batch's
             // logits, so reading a batch's table entries waits for no logits.
             const __amdgpu_buffer_rsrc_t rl = raw_buffer(vrow, (uint32_t)v1 * 16u);
-            const __amdgpu_buffer_rsrc_t rm = raw_buffer(mbytes - moff, (uint32_t)v1);
-            load_masks_buf<THREADS, U>(ma, rm, v0);
-            load_masks_buf<THREADS, U>(mb, rm, v0 + kStep);
+            const __amdgpu_buffer_rsrc_t rm = raw_buffer(mbytes - moff, mask_bytes<DT>(v1));
+            load_masks_buf<DT, THREADS, U>(ma, rm, v0);
+            load_masks_buf<DT, THREADS, U>(mb, rm, v0 + kStep);
             __builtin_amdgcn_sched_barrier(0);
             load_batch_buf<THREADS, U>(db, rl, v0 + kStep);
             __builtin_amdgcn_sched_barrier(0);
+            own(ma, v0);
             entries(la, ma);
 #define DV_STREAM_BATCH(D, L, LN, M, MN, K)                                                                    \
     {                                                                                                          \
@@ -662,9 +649,10 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
         const bool in = vb + (K) * kStep < v1; /* block-uniform */                                             \
         const uint32_t any = in ? fold(D, L, M, km) : 0u;                                                      \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
-        load_masks_buf<THREADS, U>(M, rm, vb + ((K) + 2) * kStep);                                             \
+        load_masks_buf<DT, THREADS, U>(M, rm, vb + ((K) + 2) * kStep);                                             \
         load_batch_buf<THREADS, U>(D, rl, vb + ((K) + 2) * kStep);                                             \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
+        own(MN, vb + ((K) + 1) * kStep);                                                                       \
         entries(LN, MN);                                                                                       \
         if (in)                                                                                                \
             reduce(km, any, vb + (K) * kStep);                                                                 \
@@ -682,18 +670,19 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
             // batches per trip, so no register holding a load in flight is
             // ever copied (a copy would wait for the load).
             const __amdgpu_buffer_rsrc_t rl = raw_buffer(vrow, (uint32_t)v1 * 16u);
-            const __amdgpu_buffer_rsrc_t rm = raw_buffer(mbytes - moff, (uint32_t)v1);
-            uint32_t mc[U], md[U];
+            const __amdgpu_buffer_rsrc_t rm = raw_buffer(mbytes - moff, mask_bytes<DT>(v1));
+            uint32_t mc[U], md[U], sel[U];
             // (the mask bytes that choose the third and fourth batches are
             // issued ahead of the second batch, so choosing them waits for
             // no logits)
-            load_masks_buf<THREADS, U>(ma, rm, v0);
-            load_masks_buf<THREADS, U>(mb, rm, v0 + kStep);
-            load_masks_buf<THREADS, U>(mc, rm, v0 + 2 * kStep);
-            load_masks_buf<THREADS, U>(md, rm, v0 + 3 * kStep);
+            load_masks_buf<DT, THREADS, U>(ma, rm, v0);
+            load_masks_buf<DT, THREADS, U>(mb, rm, v0 + kStep);
+            load_masks_buf<DT, THREADS, U>(mc, rm, v0 + 2 * kStep);
+            load_masks_buf<DT, THREADS, U>(md, rm, v0 + 3 * kStep);
             __builtin_amdgcn_sched_barrier(0);
             load_batch_buf<THREADS, U>(db, rl, v0 + kStep);
             __builtin_amdgcn_sched_barrier(0);
+            own(ma, v0);
             entries(la, ma);
 #define DV_AHEAD2_BATCH(D, L, LN, M, MN, MSEL, K)                                                              \
     {                                                                                                          \
@@ -701,10 +690,12 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
         const bool in = vb + (K) * kStep < v1; /* block-uniform */                                             \
         const uint32_t any = in ? fold(D, L, M, km) : 0u;                                                      \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
-        load_batch_buf_sel<THREADS, U>(D, rl, vb + ((K) + 2) * kStep, MSEL);                                   \
+        choose(sel, MSEL);                                                                                     \
+        load_batch_buf_sel<THREADS, U>(D, rl, vb + ((K) + 2) * kStep, sel);                                    \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
-        load_masks_buf<THREADS, U>(M, rm, vb + ((K) + 4) * kStep);                                             \
+        load_masks_buf<DT, THREADS, U>(M, rm, vb + ((K) + 4) * kStep);                                             \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
+        own(MN, vb + ((K) + 1) * kStep);                                                                       \
         entries(LN, MN);                                                                                       \
         if (in)                                                                                                \
             reduce(km, any, vb + (K) * kStep);                                                                 \
@@ -730,10 +721,10 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
             };
             load_masks(ma, v0);
             for (int vb = v0; vb < v1; vb += 2 * kStep) {
-                load_batch_bf16<THREADS, U>(db, vrow, vb + kStep, v1);
+                load_batch<THREADS, U>(db, vrow, vb + kStep, v1);
                 load_masks(mb, vb + kStep);
                 process_batch(da, ma, vb);
-                load_batch_bf16<THREADS, U>(da, vrow, vb + 2 * kStep, v1);
+                load_batch<THREADS, U>(da, vrow, vb + 2 * kStep, v1);
                 load_masks(ma, vb + 2 * kStep);
                 if (vb + kStep < v1)  // block-uniform
                     process_batch(db, mb, vb + kStep);
@@ -742,9 +733,9 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
         }
     }
     if (first)
-        scan_exact<1, THREADS, MASKED>(row, arow, 0, rs.head, lane_key, lane_idx);
+        scan_exact<DT, THREADS, MASKED>(row, arow, 0, rs.head, lane_key, lane_idx);
     if (last)
-        scan_exact<1, THREADS, MASKED>(row, arow, rs.head + rs.nvec * kVec, V, lane_key, lane_idx);
+        scan_exact<DT, THREADS, MASKED>(row, arow, rs.head + rs.nvec * kVec, V, lane_key, lane_idx);
     const uint64_t mine = pack(lane_key, lane_idx);
     const uint64_t vec_best = pack(best_key, best_idx);
     vec_pack = vec_best;
@@ -756,16 +747,16 @@ __device__ __forceinline__ uint64_t scan_bf16(const char *row, const uint32_t *a
 // ANY_ALIGN false: the caller has checked that every row is 16-byte aligned,
 // so only the aligned scan is compiled (fewer registers: more resident
 // blocks where several share a CU).
-template <int THREADS, int U, bool MASKED, bool ANY_ALIGN, bool STAGED, bool SELECT, bool AHEAD2 = false>
-__device__ __forceinline__ uint64_t scan_chunk_bf16(const char *row, const uint32_t *arow, const uint8_t *mbytes,
+template <int DT, int THREADS, int U, bool MASKED, bool ANY_ALIGN, bool STAGED, bool SELECT, bool AHEAD2 = false>
+__device__ __forceinline__ uint64_t scan_chunk(const char *row, const uint32_t *arow, const uint8_t *mbytes,
                                                     int moff, const int32_t *ns_row, RowSplit rs, int v0, int v1,
                                                     bool first, bool last, int V, const uint4 *lut, uint4 (&da)[U],
                                                     uint4 (&db)[U], uint64_t &vec_pack, int &vec_ns)
 {
     if (!ANY_ALIGN || rs.head == 0)
-        return scan_bf16<THREADS, U, MASKED, false, STAGED, SELECT, AHEAD2>(
+        return scan_rows<DT, THREADS, U, MASKED, false, STAGED, SELECT, AHEAD2>(
             row, arow, mbytes, moff, ns_row, rs, v0, v1, first, last, V, lut, da, db, vec_pack, vec_ns);
-    return scan_bf16<THREADS, U, MASKED, true, STAGED, SELECT>(row, arow, mbytes, moff, ns_row, rs, v0, v1, first,
+    return scan_rows<DT, THREADS, U, MASKED, true, STAGED, SELECT>(row, arow, mbytes, moff, ns_row, rs, v0, v1, first,
                                                                last, V, lut, da, db, vec_pack, vec_ns);
 }
 
@@ -800,21 +791,22 @@ __device__ __forceinline__ void stage_mask_words(uint32_t *lds, const uint32_t *
 // LDS bytes of a launch's staged mask words (chunks of chunk_vec vectors).
 inline size_t staged_mask_bytes(int chunk_vec) { return ((size_t)chunk_vec / 4 + 1) * 4; }
 
-template <int THREADS, int U, bool ANY_ALIGN, bool SELECT, bool AHEAD2>
-__global__ __launch_bounds__(THREADS) void masked_step_bf16_kernel(
+template <int DT, int THREADS, int U, bool ANY_ALIGN, bool SELECT, bool AHEAD2>
+__device__ __forceinline__ void masked_step_chunk(
     const int32_t *__restrict__ next_state, const uint32_t *__restrict__ allow, int S, int V, int W,
-    const int32_t *__restrict__ states, const void *__restrict__ logits, RowMap map, int chunk_vec,
-    int nchunks, int32_t *__restrict__ token, int32_t *__restrict__ new_state, RowMeet meet)
+    const int32_t *__restrict__ states, const void *__restrict__ logits, const RowMap &map, int chunk_vec,
+    int nchunks, int32_t *__restrict__ token, int32_t *__restrict__ new_state, const RowMeet &meet)
 {
+    static_assert(DT == 1 || !SELECT, "fp32 launches do not stage their mask bytes");
     extern __shared__ uint32_t staged[];  // the chunk's mask words
-    __shared__ uint4 lut[256];
+    __shared__ uint4 lut[DT == 1 ? 256 : 1];
     const int b = blockIdx.x / nchunks;
     const int c = blockIdx.x - b * nchunks;
-    const char *row = static_cast<const char *>(logits) + (size_t)map.offset(b) * 2;
-    const RowSplit rs = split_row(row, V);  // block-uniform
+    const char *row = static_cast<const char *>(logits) + (size_t)map.offset(b) * Elt<DT>::kBytes;
+    const RowSplit rs = split_row<DT>(row, V);  // block-uniform
     const int v0 = c * chunk_vec;            // a multiple of 4: staging starts at word v0 / 4
     const int v1 = min(rs.nvec, v0 + chunk_vec);
-    const char *vrow = row + 2 * rs.head;
+    const char *vrow = row + Elt<DT>::kBytes * rs.head;
 
     // The first batch of logits does not depend on the row's state: it is in
     // flight before the state lookup returns.  With SELECT the chunk's mask
@@ -824,7 +816,7 @@ __global__ __launch_bounds__(THREADS) void masked_step_bf16_kernel(
     // logits.  Either way the mask table is built meanwhile.
     uint4 da[U], db[U];
     if (v0 < v1)
-        load_batch_bf16<THREADS, U>(da, vrow, v0, v1);
+        load_batch<THREADS, U>(da, vrow, v0, v1);
     const int s = row_state(states, map, next_state, allow, S, V, b);
     const bool live = (uint32_t)s < (uint32_t)S;  // block-uniform
     const uint32_t *arow = allow + (size_t)(live ? s : 0) * W;
@@ -836,10 +828,10 @@ __global__ __launch_bounds__(THREADS) void masked_step_bf16_kernel(
         if (live && v0 < v1) {
             const int w0 = v0 >> 2, nwords = min(W, (v1 >> 2) + 1) - w0;  // bytes v0 .. v1
             stage_mask_words<THREADS>(staged, arow, w0, nwords, W,
-                                      [&] { load_batch_bf16<THREADS, U>(db, vrow, v0 + THREADS * U, v1); });
+                                      [&] { load_batch<THREADS, U>(db, vrow, v0 + THREADS * U, v1); });
             fill_lut(lut);
             lds_barrier();
-            mine = scan_chunk_bf16<THREADS, U, true, ANY_ALIGN, true, true>(
+            mine = scan_chunk<DT, THREADS, U, true, ANY_ALIGN, true, true>(
                 row, arow, reinterpret_cast<const uint8_t *>(staged), v0, next_state + (size_t)s * V, rs, v0, v1,
                 c == 0, c == nchunks - 1, V, lut, da, db, vec_pack, vec_ns);
         } else if (live) {  // no whole vector in this chunk: the head and tail elements only
@@ -854,10 +846,12 @@ __global__ __launch_bounds__(THREADS) void masked_step_bf16_kernel(
     } else {
         // Mask bytes read from the allow row batch by batch, right behind
         // their logits: nothing to wait for before the first batch.
-        fill_lut(lut);
-        lds_barrier();
+        if constexpr (DT == 1) {
+            fill_lut(lut);
+            lds_barrier();
+        }
         if (live)
-            mine = scan_chunk_bf16<THREADS, U, true, ANY_ALIGN, false, false, AHEAD2>(
+            mine = scan_chunk<DT, THREADS, U, true, ANY_ALIGN, false, false, AHEAD2>(
                 row, arow, reinterpret_cast<const uint8_t *>(arow), 0, next_state + (size_t)s * V, rs, v0, v1,
                 c == 0, c == nchunks - 1, V, lut, da, db, vec_pack, vec_ns);
     }
@@ -867,6 +861,19 @@ __global__ __launch_bounds__(THREADS) void masked_step_bf16_kernel(
         return;
     const int tok = best ? (int)(0xFFFFFFFFu - (uint32_t)best) : -1;
     const bool found = tok >= 0 && tok < V;  // always true for a found token; guards the read
+    if constexpr (DT == 0) {
+        // The meeting word of an fp32 row is its exact packed maximum: the
+        // last block reads the winner's next state unless the winner is its
+        // own.
+        uint64_t fin = best;
+        if (nchunks > 1 && !meet_row(meet, b, c, nchunks, best, fin))
+            return;  // another block of the row finishes it
+        const int ftok = fin ? (int)(0xFFFFFFFFu - (uint32_t)fin) : -1;
+        const bool ok = ftok >= 0 && ftok < V;
+        token[b] = ok ? ftok : -1;
+        new_state[b] = !ok ? -1 : fin == best && ns != kNsUnknown ? ns : next_state[(size_t)s * V + ftok];
+        return;
+    }
     const int nsv = !found ? -1 : ns != kNsUnknown ? ns : next_state[(size_t)s * V + tok];
     if (nchunks == 1) {
         token[b] = found ? tok : -1;
@@ -884,6 +891,27 @@ __global__ __launch_bounds__(THREADS) void masked_step_bf16_kernel(
     new_state[b] = fns != kNsUnknown ? fns : next_state[(size_t)s * V + ftok];
 }
 
+template <int THREADS, int U, bool ANY_ALIGN, bool SELECT, bool AHEAD2>
+__global__ __launch_bounds__(THREADS) void masked_step_bf16_kernel(
+    const int32_t *__restrict__ next_state, const uint32_t *__restrict__ allow, int S, int V, int W,
+    const int32_t *__restrict__ states, const void *__restrict__ logits, RowMap map, int chunk_vec,
+    int nchunks, int32_t *__restrict__ token, int32_t *__restrict__ new_state, RowMeet meet)
+{
+    masked_step_chunk<1, THREADS, U, ANY_ALIGN, SELECT, AHEAD2>(next_state, allow, S, V, W, states, logits, map,
+                                                                chunk_vec, nchunks, token, new_state, meet);
+}
+
+// fp32 rows.
+template <int THREADS, int U, bool ANY_ALIGN, bool AHEAD2>
+__global__ __launch_bounds__(THREADS) void masked_step_kernel(
+    const int32_t *__restrict__ next_state, const uint32_t *__restrict__ allow, int S, int V, int W,
+    const int32_t *__restrict__ states, const void *__restrict__ logits, RowMap map, int chunk_vec,
+    int nchunks, int32_t *__restrict__ token, int32_t *__restrict__ new_state, RowMeet meet)
+{
+    masked_step_chunk<0, THREADS, U, ANY_ALIGN, false, AHEAD2>(next_state, allow, S, V, W, states, logits, map,
+                                                               chunk_vec, nchunks, token, new_state, meet);
+}
+
 // Opportunistic masking (Sec. 3.5, further optimizations), one block per
 // row: the model's own choice over the whole row is found first, without
 // reading the mask; only when the mask does not allow it is the row scanned
@@ -898,11 +926,11 @@ __global__ __launch_bounds__(THREADS) void opportunistic_step_bf16_kernel(
     __shared__ int miss;
     const int b = blockIdx.x;
     const char *row = static_cast<const char *>(logits) + (size_t)map.offset(b) * 2;
-    const RowSplit rs = split_row(row, V);  // block-uniform
+    const RowSplit rs = split_row<1>(row, V);  // block-uniform
 
     uint4 da[U], db[U];  // db: scratch of the scan
     if (rs.nvec > 0)
-        load_batch_bf16<THREADS, U>(da, row + 2 * rs.head, 0, rs.nvec);
+        load_batch<THREADS, U>(da, row + 2 * rs.head, 0, rs.nvec);
     const int s = states[b];
     fill_lut(lut);
     lds_barrier();
@@ -912,7 +940,7 @@ __global__ __launch_bounds__(THREADS) void opportunistic_step_bf16_kernel(
     uint64_t mine = 0, vec_pack = 0;
     int vec_ns = kNsUnknown, ns;
     if (live)
-        mine = scan_chunk_bf16<THREADS, U, false, ANY_ALIGN, false, false>(
+        mine = scan_chunk<1, THREADS, U, false, ANY_ALIGN, false, false>(
             row, arow, reinterpret_cast<const uint8_t *>(arow), 0, ns_row, rs, 0, rs.nvec, true, true, V, lut, da, db,
             vec_pack, vec_ns);
     uint64_t best = block_max_ns<THREADS>(mine, vec_pack, vec_ns, ns);
@@ -924,8 +952,8 @@ __global__ __launch_bounds__(THREADS) void opportunistic_step_bf16_kernel(
     __syncthreads();
     if (miss) {  // block-uniform
         if (rs.nvec > 0)
-            load_batch_bf16<THREADS, U>(da, row + 2 * rs.head, 0, rs.nvec);
-        mine = scan_chunk_bf16<THREADS, U, true, ANY_ALIGN, false, false>(
+            load_batch<THREADS, U>(da, row + 2 * rs.head, 0, rs.nvec);
+        mine = scan_chunk<1, THREADS, U, true, ANY_ALIGN, false, false>(
             row, arow, reinterpret_cast<const uint8_t *>(arow), 0, ns_row, rs, 0, rs.nvec, true, true, V, lut, da, db,
             vec_pack, vec_ns);
         best = block_max_ns<THREADS>(mine, vec_pack, vec_ns, ns);
@@ -954,7 +982,7 @@ __global__ __launch_bounds__(THREADS) void opportunistic_step_bf16_kernel(
 // staged form, with fewer registers and so more resident blocks, stays
 // ahead (B = 256 x 9 x 128256: 70.2-70.7 against 71.9-72.5).  Shorter
 // chunks are over before the two-ahead form pays for its longer start.
-constexpr int kAhead2MinVec = 8 * kBigThreads * kBigU;
+constexpr int kAhead2MinVec = 8 * kThreads * kU;
 
 static bool skip_unread_lines(unsigned blocks)
 {
@@ -971,21 +999,31 @@ hipError_t launch_masked_rows(const int32_t *next_state, const uint32_t *allow, 
     const StepGeometry g = step_geometry(B, V, dtype);
     const RowMeet meet = row_meet(workspace, B);
     const unsigned grid = (unsigned)B * (unsigned)g.nchunks;
-    if (dtype == 0)
-        masked_step_kernel<kSmallThreads, kSmallU><<<grid, kSmallThreads, 0, stream>>>(
-            next_state, allow, S, V, W, states, logits, map, g.chunk_vec, g.nchunks, token, new_state, meet);
-    else {
+    // long chunks at up to four blocks per compute unit choose their
+    // loads from mask bytes read two batches ahead; more blocks per unit
+    // stage the mask bytes in LDS (the bf16 two-ahead scan's registers allow
+    // fewer resident blocks; fp32 chunks have no staged form)
+    const int cus = device_compute_units();
+    if (dtype == 0) {
+        const bool aligned = map.rows_aligned(logits, 4);
+        const bool ahead2 = g.chunk_vec >= kAhead2MinVec;
+#define DV_STEP_F32(A, A2)                                                                                     \
+    masked_step_kernel<kThreads, kU, A, A2><<<grid, kThreads, 0, stream>>>(                                    \
+        next_state, allow, S, V, W, states, logits, map, g.chunk_vec, g.nchunks, token, new_state, meet)
+        if (!aligned)
+            DV_STEP_F32(true, false);
+        else if (ahead2)
+            DV_STEP_F32(false, true);
+        else
+            DV_STEP_F32(false, false);
+#undef DV_STEP_F32
+    } else {
         const bool aligned = map.rows_aligned(logits, 2);
-        // long chunks at up to four blocks per compute unit choose their
-        // loads from mask bytes read two batches ahead; more blocks per unit
-        // stage the mask bytes in LDS (the two-ahead scan's registers allow
-        // fewer resident blocks)
-        const int cus = device_compute_units();
         const bool ahead2 = g.chunk_vec >= kAhead2MinVec && (cus <= 0 || grid <= 4u * (unsigned)cus);
         const bool select = !ahead2 && skip_unread_lines(grid);
         const size_t lds = select ? staged_mask_bytes(g.chunk_vec) : 0;
 #define DV_STEP_BF16(A, SEL, A2)                                                                               \
-    masked_step_bf16_kernel<kBigThreads, kBigU, A, SEL, A2><<<grid, kBigThreads, lds, stream>>>(              \
+    masked_step_bf16_kernel<kThreads, kU, A, SEL, A2><<<grid, kThreads, lds, stream>>>(              \
         next_state, allow, S, V, W, states, logits, map, g.chunk_vec, g.nchunks, token, new_state, meet)
         if (aligned && select)
             DV_STEP_BF16(false, true, false);
@@ -1016,10 +1054,10 @@ hipError_t launch_masked_step_opportunistic(const int32_t *next_state, const uin
     if (dtype == 1 && step_geometry(B, V, 1).nchunks == 1) {
         const RowMap map{ld, 0, 1, nullptr, 0};
         if (map.rows_aligned(logits, 2))
-            opportunistic_step_bf16_kernel<kBigThreads, kBigU, false><<<(unsigned)B, kBigThreads, 0, stream>>>(
+            opportunistic_step_bf16_kernel<kThreads, kU, false><<<(unsigned)B, kThreads, 0, stream>>>(
                 next_state, allow, S, V, (V + 31) / 32, states, logits, map, token, new_state);
         else
-            opportunistic_step_bf16_kernel<kBigThreads, kBigU, true><<<(unsigned)B, kBigThreads, 0, stream>>>(
+            opportunistic_step_bf16_kernel<kThreads, kU, true><<<(unsigned)B, kThreads, 0, stream>>>(
                 next_state, allow, S, V, (V + 31) / 32, states, logits, map, token, new_state);
         return hipGetLastError();
     }

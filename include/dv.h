@@ -204,10 +204,9 @@ DV_API size_t dv_masked_step_workspace_bytes(int32_t batch, int32_t num_tokens);
  *   states     [B] int32.
  *   logits     [B][ld_logits] of `dtype` (dv_dtype), row stride ld_logits
  *              elements (ld_logits >= V); the pointer must be aligned to
- *              the element size.  bf16 rows of any such alignment take the
- *              vector path (up to 7 elements before the row's first 16-byte
- *              boundary are read one by one); fp32 rows not 16-byte aligned
- *              take a scalar path with the same results.
+ *              the element size.  Rows of any such alignment take the
+ *              vector path (the elements before the row's first 16-byte
+ *              boundary are read one by one).
  * Outputs (device): token [B] int32, new_state [B] int32.  They must not
  *   overlap each other or any input (callers ping-pong two state buffers).
  * Workspace: at least dv_masked_step_workspace_bytes(B, V) bytes of device

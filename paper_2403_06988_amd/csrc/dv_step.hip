@@ -46,9 +46,15 @@
 //     differs from the exact ordering only for NaN (which must rank as -inf)
 //     and -0.0 (which must tie with +0.0); a batch whose maximum is one of
 //     those few key values is redone with exact keys.
-//   * A bf16 row need not be 16-byte aligned (any row stride): the elements
+//   * A row need not be 16-byte aligned (any row stride): the elements
 //     before its first 16-byte boundary are read one by one and the mask
-//     bits of each vector are taken from two mask bytes, shifted.
+//     bits of each vector are taken from two mask bytes, shifted.  Such
+//     vectors are as aligned as any, so they are read as raw buffers and
+//     chosen by their mask bits too; the two bytes are one unaligned 16-bit
+//     load.  us per step against clamped loads of every line and a load per
+//     mask byte (5 % of the tokens allowed): bf16 256 x 128,257 13.4 and
+//     14.5, 1,024 x 128,257 42.8 and 46.7; fp32 (two mask words per vector
+//     before) 128 x 128,257 12.4 and 25.5, 64 x 50,257 6.8 and 9.2.
 //   * fp32 rows take the same launch shapes and the same scan: 4 elements a
 //     vector, whose mask bits are half of a mask byte, and one 32-bit fast
 //     key per element, ANDed with its mask bit spread over the word (five
@@ -317,6 +323,22 @@ __device__ __forceinline__ void load_batch_buf_sel(uint4 (&d)[U], __amdgpu_buffe
     }
 }
 
+// The same where the row is shifted: the two bytes that hold the bits of
+// vector v, at head + kVec v.  Loads are branch-free: a lane past the row
+// reads its last two bytes (`last` is the second to last), and its bits are
+// zeroed when they are used.
+template <int DT, int THREADS, int U>
+__device__ __forceinline__ void load_masks_shifted(uint32_t (&m)[U], const uint8_t *mbytes, int head, int last, int vb)
+{
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t byte = (uint32_t)(head + Elt<DT>::kVec * (vb + u * THREADS + (int)threadIdx.x)) >> 3;
+        uint16_t two;  // at any byte: one unaligned load
+        __builtin_memcpy(&two, mbytes + min(byte, (uint32_t)last), 2);
+        m[u] = two;
+    }
+}
+
 // The mask bytes of aligned vectors: one per bf16 vector, one per two fp32
 // vectors.
 template <int DT>
@@ -340,8 +362,9 @@ __device__ __forceinline__ void load_masks_buf(uint32_t (&m)[U], __amdgpu_buffer
 // fewer than 8 elements.  Vector v holds elements head + 8v .. head + 8v + 7,
 // whose mask bits are bits head .. head + 7 of allow bytes v and v + 1 (just
 // byte v when head = 0).  An fp32 row is split alike, by 4 elements: vector
-// v's mask bits are bits head + 4v .. head + 4v + 3 of the allow row.  Rows of any alignment (any row stride) thus take
-// the vector path; the head and the tail are scanned element by element.
+// v's mask bits are bits head + 4v .. head + 4v + 3 of the allow row.  Rows
+// of any alignment (any row stride) thus take the vector path; the head and
+// the tail are scanned element by element.
 struct RowSplit {
     int head;  // elements before the first 16-byte boundary (fewer than a vector holds)
     int nvec;  // 16-byte vectors after the head
@@ -352,7 +375,13 @@ __device__ __forceinline__ RowSplit split_row(const char *row, int V)
 {
     const int head =
         min(V, (int)(((16u - (uint32_t)(reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) / (unsigned)Elt<DT>::kBytes));
-    return {head, (V - head) / Elt<DT>::kVec};
+    int nvec = (V - head) / Elt<DT>::kVec;
+    // A shifted vector's mask bits are read as two bytes; an fp32 vector
+    // whose bits all lie in the last byte of its allow row would read one
+    // byte past the row, so it is left to the tail.
+    if (DT == 0 && head > 0 && nvec > 0 && (head + 4 * (nvec - 1)) / 8 + 1 >= (V + 31) / 32 * 4)
+        --nvec;
+    return {head, nvec};
 }
 
 // This lane's packed best (exact key << 32 | ~index, 0 if none) over the
@@ -425,12 +454,14 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
         // for every earlier one), so while a batch is reduced the next is in
         // flight.
         //
-        // The mask bits of a streamed batch as the buffer loads bring them: a
-        // bf16 vector's own byte, or the byte that an fp32 vector shares with
-        // its neighbour, whose half is the lane's parity (a batch starts at
-        // an even vector).
-        const uint32_t half = (uint32_t)(tid & 1) * 4u;
-        auto bits_of = [&](uint32_t m) { return DT == 1 ? m : __builtin_amdgcn_ubfe(m, half, 4u); };
+        // The mask bits of a streamed batch as its loads bring them: a bf16
+        // vector's own byte, the byte that an fp32 vector shares with its
+        // neighbour, or the two bytes of a shifted vector.  Where in them the
+        // bits begin does not depend on the batch (it starts at an even
+        // vector).
+        const uint32_t at = SHIFTED ? (uint32_t)(head + kVec * tid) & 7u : (uint32_t)(kVec * tid) & 7u;
+        constexpr bool kOwnByte = DT == 1 && !SHIFTED;
+        auto bits_of = [&](uint32_t m) { return kOwnByte ? m : __builtin_amdgcn_ubfe(m, at, (uint32_t)kVec); };
         // Mask bytes with the lanes past the chunk zeroed (the buffer loads
         // of the aligned streaming bf16 scans already read zeros there; an
         // fp32 chunk's last byte may hold bits of the vector past its end).
@@ -457,9 +488,10 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
                 }
             }
         };
-        // a streamed batch's own mask bits, in place (nothing to do for bf16)
+        // a streamed batch's own mask bits, in place (nothing to do for a
+        // vector with a byte of its own)
         auto own = [&](uint32_t (&m)[U], int vb) {
-            if constexpr (DT == 0) {
+            if constexpr (!kOwnByte) {
 #pragma unroll
                 for (int u = 0; u < U; ++u)
                     m[u] = bits_of(m[u]);
@@ -575,6 +607,14 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
                 }
             }
         };
+        // The mask bits of a streamed batch, as loaded (mbytes: the allow row).
+        const __amdgpu_buffer_rsrc_t rm = raw_buffer(mbytes - moff, mask_bytes<DT>(v1));
+        auto load_bits = [&](uint32_t (&m)[U], int vb) {
+            if constexpr (SHIFTED)
+                load_masks_shifted<DT, THREADS, U>(m, mbytes, head, (V + 31) / 32 * 4 - 2, vb);
+            else
+                load_masks_buf<DT, THREADS, U>(m, rm, vb);
+        };
         uint32_t ma[U], mb[U];
         uint4 la[U], lb[U];  // mask-table entries of the batch being folded and of the next
         if constexpr (STAGED) {
@@ -585,7 +625,7 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
             // ahead, and serve both its addresses and its fold.
             const __amdgpu_buffer_rsrc_t rl = raw_buffer(vrow, (uint32_t)v1 * 16u);
             auto issue = [&](uint4 (&d)[U], int vb, const uint32_t (&sel)[U]) {
-                if constexpr (SELECT && MASKED && !SHIFTED)
+                if constexpr (SELECT && MASKED)
                     load_batch_buf_sel<THREADS, U>(d, rl, vb, sel);
                 else
                     load_batch<THREADS, U>(d, vrow, vb, v1);
@@ -631,13 +671,12 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
                 // load in flight where the branches join)
                 best_ns = ns_row[best_idx];
             }
-        } else if constexpr (MASKED && !SHIFTED && !AHEAD2) {
+        } else if constexpr (MASKED && !AHEAD2 && !(DT == 1 && SHIFTED)) {
             // Mask bytes one batch ahead, each issued before its batch's
             // logits, so reading a batch's table entries waits for no logits.
             const __amdgpu_buffer_rsrc_t rl = raw_buffer(vrow, (uint32_t)v1 * 16u);
-            const __amdgpu_buffer_rsrc_t rm = raw_buffer(mbytes - moff, mask_bytes<DT>(v1));
-            load_masks_buf<DT, THREADS, U>(ma, rm, v0);
-            load_masks_buf<DT, THREADS, U>(mb, rm, v0 + kStep);
+            load_bits(ma, v0);
+            load_bits(mb, v0 + kStep);
             __builtin_amdgcn_sched_barrier(0);
             load_batch_buf<THREADS, U>(db, rl, v0 + kStep);
             __builtin_amdgcn_sched_barrier(0);
@@ -649,7 +688,7 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
         const bool in = vb + (K) * kStep < v1; /* block-uniform */                                             \
         const uint32_t any = in ? fold(D, L, M, km) : 0u;                                                      \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
-        load_masks_buf<DT, THREADS, U>(M, rm, vb + ((K) + 2) * kStep);                                             \
+        load_bits(M, vb + ((K) + 2) * kStep);                                                                  \
         load_batch_buf<THREADS, U>(D, rl, vb + ((K) + 2) * kStep);                                             \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
         own(MN, vb + ((K) + 1) * kStep);                                                                       \
@@ -663,22 +702,21 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
                 best_ns = ns_row[best_idx];  // as above
             }
 #undef DV_STREAM_BATCH
-        } else if constexpr (MASKED && !SHIFTED) {
+        } else if constexpr (MASKED && AHEAD2) {
             // Mask bytes two batches ahead of their logits: each batch from
             // the third on is issued with its vectors' offsets chosen by
             // them, so a vector with no allowed token is not read.  Four
             // batches per trip, so no register holding a load in flight is
             // ever copied (a copy would wait for the load).
             const __amdgpu_buffer_rsrc_t rl = raw_buffer(vrow, (uint32_t)v1 * 16u);
-            const __amdgpu_buffer_rsrc_t rm = raw_buffer(mbytes - moff, mask_bytes<DT>(v1));
             uint32_t mc[U], md[U], sel[U];
             // (the mask bytes that choose the third and fourth batches are
             // issued ahead of the second batch, so choosing them waits for
             // no logits)
-            load_masks_buf<DT, THREADS, U>(ma, rm, v0);
-            load_masks_buf<DT, THREADS, U>(mb, rm, v0 + kStep);
-            load_masks_buf<DT, THREADS, U>(mc, rm, v0 + 2 * kStep);
-            load_masks_buf<DT, THREADS, U>(md, rm, v0 + 3 * kStep);
+            load_bits(ma, v0);
+            load_bits(mb, v0 + kStep);
+            load_bits(mc, v0 + 2 * kStep);
+            load_bits(md, v0 + 3 * kStep);
             __builtin_amdgcn_sched_barrier(0);
             load_batch_buf<THREADS, U>(db, rl, v0 + kStep);
             __builtin_amdgcn_sched_barrier(0);
@@ -693,7 +731,7 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
         choose(sel, MSEL);                                                                                     \
         load_batch_buf_sel<THREADS, U>(D, rl, vb + ((K) + 2) * kStep, sel);                                    \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
-        load_masks_buf<DT, THREADS, U>(M, rm, vb + ((K) + 4) * kStep);                                             \
+        load_bits(M, vb + ((K) + 4) * kStep);                                                                  \
         __builtin_amdgcn_sched_barrier(0);                                                                     \
         own(MN, vb + ((K) + 1) * kStep);                                                                       \
         entries(LN, MN);                                                                                       \
@@ -709,8 +747,12 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
             }
 #undef DV_AHEAD2_BATCH
         } else {
-            // rows of any alignment, and the unmasked scan: the same parts
-            // in sequence, the next batch's loads issued ahead of each
+            // the unmasked scan and shorter chunks of shifted bf16 rows: the
+            // same parts in sequence, the next batch's loads issued ahead of
+            // each (for the latter 2-5 % faster than the streamed form at one
+            // or two batches, which waits in each batch for the next one's
+            // mask bytes: B = 100 x V = 50,257 in two chunks 6.5 against 6.7
+            // us; 2 % slower at six, 200 x 50,257 7.9 against 7.7)
             auto process_batch = [&](const uint4 (&d)[U], uint32_t (&m)[U], int vb) {
                 live(m, vb);
                 uint4 l[U];
@@ -756,7 +798,7 @@ __device__ __forceinline__ uint64_t scan_chunk(const char *row, const uint32_t *
     if (!ANY_ALIGN || rs.head == 0)
         return scan_rows<DT, THREADS, U, MASKED, false, STAGED, SELECT, AHEAD2>(
             row, arow, mbytes, moff, ns_row, rs, v0, v1, first, last, V, lut, da, db, vec_pack, vec_ns);
-    return scan_rows<DT, THREADS, U, MASKED, true, STAGED, SELECT>(row, arow, mbytes, moff, ns_row, rs, v0, v1, first,
+    return scan_rows<DT, THREADS, U, MASKED, true, STAGED, SELECT, AHEAD2>(row, arow, mbytes, moff, ns_row, rs, v0, v1, first,
                                                                last, V, lut, da, db, vec_pack, vec_ns);
 }
 
@@ -1010,12 +1052,14 @@ hipError_t launch_masked_rows(const int32_t *next_state, const uint32_t *allow, 
 #define DV_STEP_F32(A, A2)                                                                                     \
     masked_step_kernel<kThreads, kU, A, A2><<<grid, kThreads, 0, stream>>>(                                    \
         next_state, allow, S, V, W, states, logits, map, g.chunk_vec, g.nchunks, token, new_state, meet)
-        if (!aligned)
-            DV_STEP_F32(true, false);
-        else if (ahead2)
+        if (aligned && ahead2)
             DV_STEP_F32(false, true);
-        else
+        else if (aligned)
             DV_STEP_F32(false, false);
+        else if (ahead2)
+            DV_STEP_F32(true, true);
+        else
+            DV_STEP_F32(true, false);
 #undef DV_STEP_F32
     } else {
         const bool aligned = map.rows_aligned(logits, 2);

@@ -233,16 +233,19 @@ __device__ __forceinline__ bool meet_row(RowMeet m, int b, int c, int nchunks, u
 //
 // A row of V logits is split into `nchunks` chunks of `chunk_vec` 16-byte
 // vectors, one block of `threads` lanes each; with more than one chunk the
-// blocks meet in the workspace (above).  Blocks have 512 lanes.  bf16 rows
-// take one per row once B >= kStepOneBlockRows (a block per compute unit
-// already) or when B >= 64 and a row holds at most kStepSingleBlockRowBytes
-// (a second block per row buys nothing there); otherwise, and for fp32 rows
-// always, about 32 / sqrt(B) chunks per row.
+// blocks meet in the workspace (above).  Blocks have 512 lanes.  A row is one
+// block once B >= kStepOneBlockRows (a block per compute unit already) or when
+// it holds at most kStepSingleBlockBatches batches (1,024 vectors each: the
+// meeting costs more than the second block's stream saves at any B: V =
+// 16,000 bf16 in 1 and 2 chunks, us per step: B = 1 3.48 and 4.04, B = 128
+// 4.54 and 4.90; V = 24,000: B = 1 3.93 and 4.40, B = 64 4.97 and 5.05; at
+// four batches, V = 28,000 and 32,000, two chunks win from B = 2 to 64).
+// Otherwise as many chunks as step_geometry's rule gives.
 constexpr int kStepOneBlockRows = 256;
 constexpr int kStepThreads = 512;
 constexpr int kStepStageWords = 8192;    // mask words a bf16 block may stage in LDS
 constexpr int kStepMaxChunkVec = (kStepStageWords - 1) * 4 / kStepThreads * kStepThreads;
-constexpr int64_t kStepSingleBlockRowBytes = 65536;
+constexpr int kStepSingleBlockBatches = 3;
 static_assert(kStepMaxChunkVec % kStepThreads == 0, "chunks are whole batches of lanes");
 
 struct StepGeometry {
@@ -257,22 +260,39 @@ inline StepGeometry step_geometry(int B, int V, int dtype)
     const int vec = bf16 ? 8 : 4;  // elements per 16-byte vector
     const int threads = kStepThreads;
     const int nvec = V / vec;
+    const int batches = (nvec + 2 * threads - 1) / (2 * threads);  // of two vectors per lane
+    const int b = B > 0 ? B : 1;
     int want;
-    if (bf16 && B >= kStepOneBlockRows) {
+    if (b >= kStepOneBlockRows || batches <= kStepSingleBlockBatches) {
         want = 1;
-    } else if (bf16 && B >= 64 && (int64_t)V * 2 <= kStepSingleBlockRowBytes) {
-        want = 1;
+    } else if (b >= 16) {
+        // Never more than 256 blocks, one per compute unit: a 257th doubles
+        // up and the launch waits for that unit (V = 128,256 bf16, us per
+        // step: B = 100 in 2 chunks a row 8.3, in 3 10.4; B = 160 in 1 10.9,
+        // in 2 12.4; B = 200 in 1 11.4, in 2 12.9).  Within that, four chunks
+        // (they meet in pairs), and more only where each keeps four batches:
+        // B = 32 x 128,256 in 4 6.54, in 6 6.58, in 8 6.74; x 256,000 in 4
+        // 8.44, in 8 7.80.
+        const int long_row = (batches + 3) / 4;
+        want = long_row > 4 ? long_row : 4;
+        want = want < kStepOneBlockRows / b ? want : kStepOneBlockRows / b;
     } else {
-        // Chunks per row ~ 32 / sqrt(B): about 32 sqrt(B) blocks per launch
-        // (at most 256).  Since split rows meet in the workspace instead of a
-        // second kernel, this is what measures fastest from B = 1 to 128 at
-        // V = 32000 .. 256000: fewer blocks leave bandwidth unused, more
-        // make each block's stream too short for its fixed start-up cost.
+        // A few rows: about 32 sqrt(B) blocks, i.e. 32 / sqrt(B) chunks per
+        // row, fits a sweep from B = 1 to 16 at V = 32,000 .. 256,000 within
+        // 3 %: fewer blocks leave bandwidth unused, more make each block's
+        // stream too short for its fixed start-up cost.
         int r = 1;
-        while (r * r < B)
+        while (r * r < b)
             ++r;  // ceil(sqrt(B))
-        const int blocks = 32 * r < 256 ? 32 * r : 256;
-        want = (blocks + B / 2) / (B > 0 ? B : 1);
+        want = (32 * r + b / 2) / b;
+    }
+    // Rows of four batches meet in pairs at most, and at the ends of the
+    // range hardly split (V = 32,000 bf16, us per step: B = 1 in 1 4.23, in 2
+    // 4.31, in more 4.5; B = 2 in 2 4.29, in 4 4.50; B = 8 in 2 4.82, in 4
+    // 4.73; B = 64 in 1 5.33, in 2 5.21; B = 128 in 1 5.54, in 2 5.59).
+    if (batches <= 4) {
+        const int few = b == 1 || b >= 128 ? 1 : b < 4 ? 2 : 4;
+        want = want < few ? want : few;
     }
     // at least one vector per lane per chunk
     const int max_chunks = nvec / threads > 1 ? nvec / threads : 1;

@@ -4,11 +4,11 @@
 // The step reads B x V logits once: it is bound by HBM read bandwidth, so
 // the design is about keeping enough bytes in flight and spending few ALU
 // operations per element.
-//   * Launch shape (step_geometry; bf16 figures).  A row is one 512-lane block once
-//     B >= 256 (every CU gets at least one row), or when B >= 64 and the row
-//     holds at most 32768 logits (a second block per row buys nothing
-//     there).  Otherwise each row is split into about 32 / sqrt(B) chunks,
-//     one block each, and the chunks meet in the workspace (meet_row): up
+//   * Launch shape (step_geometry).  A row is one 512-lane block once B >=
+//     256 (every CU gets at least one row), or when the row holds at most
+//     three batches (24,576 bf16 logits; the meeting costs more than a second
+//     block saves).  Otherwise each row is split into chunks, one block each,
+//     never more than 256 in all, and the chunks meet in the workspace (meet_row): up
 //     to four chunks in pairs, each pair's second block learning both
 //     values from one device-scope atomic maximum (one round trip per
 //     level); more chunks through a device-scope atomic maximum and then an
@@ -1095,7 +1095,11 @@ hipError_t launch_masked_step_opportunistic(const int32_t *next_state, const uin
     // rows, rows split over several blocks, where checking first would need
     // an extra pass over the chunks) the plain masked step gives the same
     // result.
-    if (dtype == 1 && step_geometry(B, V, 1).nchunks == 1) {
+    // (Small batches of short rows and middling ones of long rows are one
+    // block each too, but there the check would add a pass to every row that
+    // fails it, with few other rows to hide it behind.)
+    const bool check = B >= kStepOneBlockRows || (B >= 64 && V <= 32768);
+    if (dtype == 1 && check && step_geometry(B, V, 1).nchunks == 1) {
         const RowMap map{ld, 0, 1, nullptr, 0};
         if (map.rows_aligned(logits, 2))
             opportunistic_step_bf16_kernel<kThreads, kU, false><<<(unsigned)B, kThreads, 0, stream>>>(

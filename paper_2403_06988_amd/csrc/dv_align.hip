@@ -31,6 +31,10 @@
 //      at 32-bit offsets (a dead state skips its read).  Stores are coalesced
 //      along tokens; the allow words come from a wave ballot (64 tokens -> 2
 //      words).
+//
+// Automata of at most kDirectStates states take one launch instead, the direct
+// walk (kernel 7): a state fits in a byte, so the table over all 256 byte
+// values fits in LDS as it is, and steps 1 to 4 fall away.
 #include <algorithm>
 
 #include "dv_internal.h"
@@ -72,6 +76,15 @@ constexpr int kTileDeferGrid = 8192;
 constexpr int kLdsPerCu = 160 * 1024;  // gfx950
 static_assert(kPrefR >= 1 && 2 * kPrefLds <= 160 * 1024, "two blocks per compute unit");
 static_assert(kPrefThreads >= 256, "one byte class per thread in the first 256");
+
+// the direct walk: at most this many states (a byte holds a state or the
+// sentinel that stands for dead), and the states a lane walks at once
+constexpr int kDirectStates = 255;
+constexpr int kDirectG = 16;
+constexpr int kDirectThreads = 1024;
+constexpr int kDirectFewThreads = 256;    // where tiles of 1,024 tokens would leave compute units idle
+constexpr int kDirectTargetBlocks = 512;  // two resident blocks of 1,024 lanes per compute unit
+constexpr int kDirectLdsMax = (kDirectStates + 1) * 256;
 
 // token lengths with a special meaning in the walk
 constexpr int kPastEnd = -1;  // a lane slot past the last token: never stored
@@ -590,6 +603,137 @@ __global__ __launch_bounds__(kPrefThreads) void walk_prefix_kernel(
     }
 }
 
+// 7. the direct walk, for at most kDirectStates states.  A block copies the
+// whole table into LDS, a byte per entry (row S, all dead, is the sentinel
+// that every dead state reads), and walks one token per lane from `groups`
+// groups of kDirectG states, one byte per iteration: kDirectG independent LDS
+// reads.  What bounds a small automaton is neither bandwidth nor arithmetic
+// but latency, launch after launch: the class pipeline in front of the walk
+// was three launches of chained loads, and a 256-lane block staged its 47 KB
+// table two bytes per lane at a time.  Here a block's loads of the table are
+// 16 bytes per lane and independent, and a token's bytes are read 8 at a time.
+// us per call, pipeline before and direct walk now: 92 states x 32,000 tokens
+// 35.0 and 13.4, 250 x 32,000 83 and 23, 200 x 128,256 98 and 42, 250 x 256,000
+// 215 and 101 (few live bytes), 255 x 256,000 776 and 152 (nearly all bytes
+// live: the LDS reads bound it).  With 4, 8 and 16 states at once the last takes
+// 300, 193 and 152 (16 reads hide one read's latency; the token's byte and the
+// loop are shared), the first 15.1, 13.6 and 13.4.
+__device__ __forceinline__ uint64_t token_bytes8(const uint8_t *__restrict__ bytes, int64_t at, int64_t end,
+                                                 int64_t total)
+{
+    uint64_t v = 0;
+    if (at >= 0 && at + 8 <= total) {
+        __builtin_memcpy(&v, bytes + at, 8);  // any alignment; bytes past the token's end are not used
+    } else {
+        const int n = (int)min((int64_t)8, end - at);
+        for (int k = 0; k < n; ++k)
+            v |= (uint64_t)bytes[at + k] << (8 * k);
+    }
+    return v;
+}
+
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void walk_direct_kernel(
+    const int32_t *__restrict__ trans, int S, const int32_t *__restrict__ offsets, const uint8_t *__restrict__ bytes,
+    int V, int W, int eos_token, int groups, const uint8_t *__restrict__ accepting,
+    int32_t *__restrict__ next_state, uint32_t *__restrict__ allow)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int t = blockIdx.x * THREADS + tid;
+
+    // the token, while the table is on its way
+    int len = kPastEnd;
+    int64_t off = 0;
+    const int64_t total = offsets[V];
+    if (t < V) {
+        off = offsets[t];
+        len = max(0, offsets[t + 1] - (int)off);  // a decreasing pair reads as an empty token
+        if (t == eos_token)
+            len = kEosLen;  // its bytes are ignored: allowed exactly in accepting states
+    }
+    const int n4 = S * 64;  // groups of four entries
+    uint32_t *tab4 = reinterpret_cast<uint32_t *>(smem);
+#pragma unroll 8
+    for (int i = tid; i < n4; i += THREADS) {
+        int32_t x[4];
+        __builtin_memcpy(x, trans + (size_t)i * 4, 16);  // one load at int32 alignment
+        uint32_t packed = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            packed |= (in_range(x[k], S) ? (uint32_t)x[k] : (uint32_t)S) << (8 * k);
+        tab4[i] = packed;
+    }
+    for (int i = tid; i < 64; i += THREADS)
+        tab4[n4 + i] = (uint32_t)S * 0x01010101u;
+    const uint64_t first8 = len > 0 ? token_bytes8(bytes, off, off + len, total) : 0;
+    __syncthreads();
+
+    const uint32_t dead = (uint32_t)S;
+    const int t0 = blockIdx.x * THREADS + wave * kWave;  // a multiple of 64
+    const int w = t0 / 32 + lane;
+    const int g_end = min(S, (int)(blockIdx.y + 1) * groups * kDirectG);
+    for (int s0 = blockIdx.y * groups * kDirectG; s0 < g_end; s0 += kDirectG) {
+        uint32_t st[kDirectG];
+#pragma unroll
+        for (int k = 0; k < kDirectG; ++k) {
+            const int s = s0 + k;
+            st[k] = s < S ? (uint32_t)s : dead;
+            if (len < 0)  // EOS: only where the scanner may stop; past the last token: dead
+                st[k] = s < S && len == kEosLen && accepting != nullptr && accepting[s] != 0 ? (uint32_t)s : dead;
+        }
+        uint64_t cur = first8;
+        for (int h = 0; h < len;) {  // an empty token keeps the state
+            const uint32_t c = (uint32_t)cur & 0xFFu;
+            cur >>= 8;
+            uint32_t m = dead;
+#pragma unroll
+            for (int k = 0; k < kDirectG; ++k) {
+                st[k] = smem[st[k] << 8 | c];
+                m = min(m, st[k]);
+            }
+            h += 1;
+            if (m == dead)
+                break;
+            if ((h & 7) == 0 && h < len)
+                cur = token_bytes8(bytes, off + h, off + len, total);
+        }
+#pragma unroll
+        for (int k = 0; k < kDirectG; ++k) {
+            const int s = s0 + k;
+            if (s >= S)
+                break;
+            const bool alive = st[k] != dead;
+            if (t < V)
+                __builtin_nontemporal_store(alive ? (int32_t)st[k] : -1, &next_state[(size_t)s * V + t]);
+            const uint64_t mask = __ballot(alive);
+            if (lane < 2 && w < W)
+                __builtin_nontemporal_store((uint32_t)(mask >> (32 * lane)), &allow[(size_t)s * W + w]);
+        }
+    }
+}
+
+template <int THREADS>
+hipError_t launch_walk_direct(const int32_t *trans, int S, const int32_t *offsets, const uint8_t *bytes, int V,
+                              const uint8_t *accepting, int eos_token, int32_t *next_state, uint32_t *allow,
+                              hipStream_t stream)
+{
+    // LDS beyond the default 64 KB per block must be opted into once.
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(walk_direct_kernel<THREADS>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kDirectLdsMax);
+    if (attr != hipSuccess)
+        return attr;
+    // A block keeps its table for as many state groups as leave
+    // kDirectTargetBlocks blocks, which covers the table's loads.
+    const long long nt = (V + THREADS - 1) / THREADS, ng = (S + kDirectG - 1) / kDirectG;
+    const long long per = std::max(1ll, nt * ng / kDirectTargetBlocks);
+    const dim3 grid((unsigned)nt, (unsigned)((ng + per - 1) / per));
+    walk_direct_kernel<THREADS><<<grid, THREADS, (S + 1) * 256, stream>>>(
+        trans, S, offsets, bytes, V, (V + 31) / 32, eos_token, (int)per, accepting, next_state, allow);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 // The vocabulary's CSR layout: the smallest t in [0, V] at which it breaks
@@ -624,6 +768,19 @@ hipError_t launch_align(const int32_t *trans, int S, const int32_t *offsets, con
                         int V, const uint8_t *accepting, int eos_token, int32_t *next_state,
                         uint32_t *allow, void *workspace, hipStream_t stream)
 {
+    if (S <= kDirectStates) {
+        // Fewer tiles than compute units: a quarter of the tokens per block
+        // fills them.  Above that the wide blocks win, since the narrow ones
+        // copy the table four times as often (250 states x 32,000 tokens, at 8
+        // states a group: 25 us in 1,024-lane blocks, 50 in 256-lane ones).
+        const long long tiles = (long long)((V + kDirectThreads - 1) / kDirectThreads) *
+                                ((S + kDirectG - 1) / kDirectG);
+        return tiles < kDirectTargetBlocks / 2
+                   ? launch_walk_direct<kDirectFewThreads>(trans, S, offsets, bytes, V, accepting, eos_token,
+                                                           next_state, allow, stream)
+                   : launch_walk_direct<kDirectThreads>(trans, S, offsets, bytes, V, accepting, eos_token,
+                                                        next_state, allow, stream);
+    }
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     uint32_t *partial = reinterpret_cast<uint32_t *>(ws + kAlignMetaBytes);
     uint16_t *table = reinterpret_cast<uint16_t *>(ws + align_table_offset(S));

@@ -11,8 +11,8 @@
 // 32x32->64 multiplies) per 4 tokens and two logarithms per token.  Only
 // admissible tokens need noise, so each wave compacts its 4-token groups
 // that hold at least one allowed token into an LDS queue (one allow word of
-// 32 tokens per lane, or half of one when few blocks are resident; ballot
-// prefix sums for the queue offsets), then every
+// 32 tokens per lane, or half of one when few blocks are resident; one
+// prefix sum over the lanes for the queue offsets), then every
 // lane takes one queued group: one Philox call per group, a logarithm pair
 // per allowed token.  Where a wave's allowed tokens are hardly more than its
 // groups (sparse masks) it queues single tokens instead, so that no lane
@@ -229,41 +229,38 @@ __device__ __forceinline__ uint4 group_logits(const char *row, bool aligned, uin
     return v;
 }
 
-// Exclusive prefix sum over the wave of a count in [0, 15], and the wave's
-// total, from four ballots of the count's bits (no LDS, no waits).
-__device__ __forceinline__ int wave_prefix_small(int cnt, int &total)
+// Inclusive prefix sum over the wave: within each row of 16 lanes by shifts of
+// 1, 2, 4 and 8 lanes, then lane 15 of rows 0 and 2 into the row above and
+// lane 31 into the upper two rows.  Two small counts share a word, so one scan
+// serves both: six adds and no scalar registers, where the ballots of the
+// counts' bits took about fifty instructions and twenty scalar registers (us
+// per step with those and now, a twentieth of the tokens allowed: 256 x 128,256
+// 20.3 and 19.7, 8 x 32,000 5.43 and 5.33, 1,024 x 32,000 22.4 and 22.0).
+// Every lane of the wave must be active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
 {
-    int excl = 0, tot = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint64_t m = __ballot((cnt >> j) & 1);
-        const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        excl += below << j;
-        tot += __popcll(m) << j;
-    }
-    total = tot;
-    return excl;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
 
-// The same for a count in [0, 32] (six ballots).
-__device__ __forceinline__ int wave_prefix_word(int cnt, int &total)
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v)
 {
-    int excl = 0, tot = 0;
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        const uint64_t m = __ballot((cnt >> j) & 1);
-        const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        excl += below << j;
-        tot += __popcll(m) << j;
-    }
-    total = tot;
-    return excl;
+    v += dpp_or_zero<0x111, 0xF>(v);  // row_shr:1
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    v += dpp_or_zero<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
 }
 
+// At most 80 scalar registers: with more a SIMD unit holds seven waves, not
+// eight, and a launch that just fills the chip (2,048 blocks of 256 lanes, 512
+// of 1,024) waits for a second round.  81 to 90 of them took 22.8 to 23.3 us
+// instead of 20.6 at 256 x 128,256 and 26.7 instead of 22.3 at 1,024 x 32,000
+// (about a twentieth of the tokens allowed).
 template <int DT, int THREADS, int SPAN>
-__global__ __launch_bounds__(THREADS) void masked_sample_kernel(
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_num_sgpr(80))) void masked_sample_kernel(
     const int32_t *__restrict__ next_state, const uint32_t *__restrict__ allow, int S, int V, int W,
     const int32_t *__restrict__ states, const void *__restrict__ logits, int64_t ld, float inv_t, uint32_t seed_lo,
     uint32_t seed_hi, uint32_t off_lo, uint32_t off_hi, int chunk_tok, int nchunks, RowMeet meet,
@@ -295,9 +292,13 @@ __global__ __launch_bounds__(THREADS) void masked_sample_kernel(
                 word &= (1u << (t1 - tok0)) - 1u;  // a chunk ends inside this span only at V
             // groups (4 tokens) holding an allowed token: bit 4k of `nz`
             uint32_t nz = (word | (word >> 1) | (word >> 2) | (word >> 3)) & 0x11111111u;
-            int groups, toks;
-            const int gpos = wave_prefix_small(__popc(nz), groups);  // at most 8 groups per lane
-            const int tpos = wave_prefix_word(__popc(word), toks);
+            // token and group counts (at most 32 and 8 per lane), one per half
+            const uint32_t counts = (uint32_t)__popc(word) | (uint32_t)__popc(nz) << 16;
+            const uint32_t upto = wave_prefix(counts);
+            const uint32_t all = lane_value(upto, kWave - 1);
+            const int toks = (int)(all & 0xFFFFu), groups = (int)(all >> 16);
+            const uint32_t before = upto - counts;
+            const int tpos = (int)(before & 0xFFFFu), gpos = (int)(before >> 16);
             // wave-uniform: single tokens when they fit the queue and are few per group
             const bool by_token = toks <= kWave * 8 && 4 * toks <= kTokenRatio4 * groups;
             if (by_token) {

@@ -13,8 +13,16 @@
 // that hold at least one allowed token into an LDS queue (one allow word of
 // 32 tokens per lane, or half of one when few blocks are resident; one
 // prefix sum over the lanes for the queue offsets), then every
-// lane takes one queued group: one Philox call per group, a logarithm pair
-// per allowed token.  Where a wave's allowed tokens are hardly more than its
+// lane takes one queued group: one Philox call per group, and a logarithm pair
+// only for the tokens whose key could still be the row's best.  A token's noise
+// has an upper bound that costs two conversions and one multiply-add
+// (gumbel_bound_of_word); a token whose logit and bound stay below the best key
+// that the block has found cannot win nor tie, so its logarithms are left out.
+// Of a dense wave's tokens that leaves one or two passes in its first trips
+// and hardly any later: us per step with a pair for every token and now, three
+// fifths of the tokens allowed: 256 x 128,256 59.4 and 35.7, 64 x 32,000 10.7
+// and 9.3, 1,024 x 16,000 35.7 and 24.2, 8 x 128,256 10.7 and 9.1; rows that
+// start at any alignment, 100 x 50,257, 20.6 and 13.0.  Where a wave's allowed tokens are hardly more than its
 // groups (sparse masks) it queues single tokens instead, so that no lane
 // waits on a neighbour's second logarithm pair; dense masks keep the groups
 // and so one Philox call per 4 tokens.  Lanes combine exact
@@ -31,13 +39,13 @@ constexpr int kRowThreads = 1024;   // one block per row once B >= kOneBlockRows
                                     // latency-laden arithmetic needs more than it saves a launch)
 constexpr int kOneBlockRows = 1024;  // four or more rows per CU keep enough waves resident
 // A wave queues single tokens instead of 4-token groups when its allowed
-// tokens number at most kTokenRatio4 / 4 times its allowed groups: a lane
-// then pays one Philox call and one logarithm pair per trip, where a group
-// trip pays as many pairs as the wave's fullest group holds (two or three
-// on almost every trip of a sparse random mask, while its groups average
-// 1.1 tokens).  Per trip a Philox call is about 63 instructions and a pair
-// about 90, so single tokens cost less up to about twice as many tokens as
-// groups; runs of allowed tokens (4 per group) keep the groups.
+// tokens number at most kTokenRatio4 / 4 times its allowed groups: a lane then
+// pays one Philox call and one logarithm pair per trip and nothing else.  Such
+// a sparse wave makes three or four trips in all, too few for bounds to rule
+// much out, while a group trip pays four bounds and the choice among them.  Us
+// per step with lines at 0, 5 and 8 (a twentieth of the tokens allowed): 256 x
+// 128,256 21.4, 21.3, 20.1; 64 x 32,000 7.9, 7.6, 7.2; 8 x 32,000 6.2, 6.3,
+// 5.4; masks of runs and of three fifths take groups at all three.
 constexpr int kTokenRatio4 = 8;
 constexpr int kTargetBlocks = 2048;
 constexpr int kHalfSpanBlocks = 512;
@@ -177,6 +185,18 @@ __device__ __forceinline__ float gumbel_of_word(uint32_t w)
     return -ln_f32(-ln_f32(u));
 }
 
+// An upper bound of gumbel_of_word(w) in one conversion each way and one
+// fused multiply-add.  -ln u >= 1 - u, so G <= -ln(1 - u); 1 - u is at least
+// 2^-32 f with f the word's complement without its low byte (exact in
+// binary32; where it is zero, 1 - u is 2^-24), and log2 f is at least its
+// linear interpolation between powers of two, which is f's bit pattern / 2^23
+// - 127.  2^-10 covers the rounding of both sides (below 2^-15 together).
+__device__ __forceinline__ float gumbel_bound_of_word(uint32_t w)
+{
+    const float f = (float)~(w | 0xFFu);
+    return __builtin_fmaf((float)__float_as_uint(f), -0x1.62e430p-24f, 0x1.b8d874p+6f);
+}
+
 // Order-preserving key of a binary32 value: NaN ranks as -inf, -0.0 as
 // +0.0; every value's key is > 0, so 0 stands for "nothing yet".  Adding
 // +0.0 turns -0.0 into +0.0 and leaves every other value as it is (round to
@@ -190,6 +210,12 @@ __device__ __forceinline__ uint32_t order_key(float x)
     return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 
+// The value of an order key; NaN (nothing is below it) of 0, "nothing yet".
+__device__ __forceinline__ float key_value(uint32_t k)
+{
+    return __uint_as_float(k & 0x80000000u ? k ^ 0x80000000u : ~k);
+}
+
 __device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
 template <int DT>
@@ -201,32 +227,59 @@ __device__ __forceinline__ float logit_at(const char *row, int i)
         return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t *>(row)[i] << 16);
 }
 
-// The 4 logits of group g (tokens 4g .. 4g+3) as binary32 bit patterns: one
-// vector load when the row is aligned to a group and the group lies inside
-// the row, else element loads of the allowed tokens only (the last group
-// may run past V).
+// The 4 logits of group g (tokens 4g .. 4g+3) as they lie in memory: one load
+// at the row's own alignment (an element at a time, rows off 8 or 16 bytes took
+// 16.8 us instead of 13.0 at 100 x 50,257).  The last group may run past V: its load ends at
+// V instead, and group_value takes that into account.  Rows of fewer than 4
+// tokens are read token by token.
 template <int DT>
-__device__ __forceinline__ uint4 group_logits(const char *row, bool aligned, uint32_t g, uint32_t bits, int V)
+struct GroupWords;
+template <>
+struct GroupWords<0> {
+    uint32_t w[4];
+};
+template <>
+struct GroupWords<1> {
+    uint64_t w;
+};
+
+template <int DT>
+__device__ __forceinline__ GroupWords<DT> load_group(const char *row, uint32_t g, int V)
 {
-    const int i0 = (int)(g * 4u);
-    if (aligned && i0 + 3 < V) {
-        if constexpr (DT == 0) {
-            return reinterpret_cast<const uint4 *>(row)[g];
-        } else {
-            const uint2 h = reinterpret_cast<const uint2 *>(row)[g];
-            return make_uint4(h.x << 16, h.x & 0xFFFF0000u, h.y << 16, h.y & 0xFFFF0000u);
-        }
+    constexpr int kElt = DT == 0 ? 4 : 2;
+    GroupWords<DT> v;
+    if (V >= 4) {
+        const int i0 = min((int)(g * 4u), V - 4);
+        __builtin_memcpy(&v, row + (size_t)i0 * kElt, 4 * kElt);
+    } else {
+        char *dst = reinterpret_cast<char *>(&v);
+        for (int e = 0; e < 4; ++e)
+            __builtin_memcpy(dst + e * kElt, row + (size_t)min(e, V - 1) * kElt, kElt);
     }
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (bits & 1u)
-        v.x = __float_as_uint(logit_at<DT>(row, i0));
-    if (bits & 2u)
-        v.y = __float_as_uint(logit_at<DT>(row, i0 + 1));
-    if (bits & 4u)
-        v.z = __float_as_uint(logit_at<DT>(row, i0 + 2));
-    if (bits & 8u)
-        v.w = __float_as_uint(logit_at<DT>(row, i0 + 3));
     return v;
+}
+
+// the logit of token 4g + e in group g's words, as a binary32 bit pattern
+template <int DT>
+__device__ __forceinline__ void group_values(GroupWords<DT> v, uint32_t g, int V, uint32_t (&x)[4])
+{
+    const int past = V >= 4 ? max((int)(g * 4u) + 4 - V, 0) : 0;  // 0 .. 3 tokens past V
+    if constexpr (DT == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            x[e] = v.w[e];
+        for (int k = 0; k < past; ++k) {
+            x[0] = x[1];
+            x[1] = x[2];
+            x[2] = x[3];
+        }
+    } else {
+        const uint64_t w = v.w >> (16 * past);
+        x[0] = (uint32_t)w << 16;
+        x[1] = (uint32_t)w & 0xFFFF0000u;
+        x[2] = (uint32_t)(w >> 32) << 16;
+        x[3] = (uint32_t)(w >> 32) & 0xFFFF0000u;
+    }
 }
 
 // Inclusive prefix sum over the wave: within each row of 16 lanes by shifts of
@@ -277,9 +330,13 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_num_sgpr(80))) void 
     const int s = states[b];
     const bool live = (uint32_t)s < (uint32_t)S;  // block-uniform
     uint64_t best = 0;
+    uint32_t wave_key = 0;          // wave-uniform order key of the best key this wave knows of
+    __shared__ uint32_t block_key;  // and of the block's, over its waves
+    if (tid == 0)
+        block_key = 0;
+    __syncthreads();
     if (live) {
         const char *row = static_cast<const char *>(logits) + (size_t)b * (size_t)ld * (DT == 0 ? 4 : 2);
-        const bool aligned = (reinterpret_cast<uintptr_t>(row) & (DT == 0 ? 15 : 7)) == 0;  // block-uniform
         const uint32_t *arow = allow + (size_t)s * W;
         const int t0 = c * chunk_tok;
         const int t1 = min(V, t0 + chunk_tok);
@@ -330,31 +387,60 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_num_sgpr(80))) void 
                     best = max_u64(best, packed);
                 }
             } else {
-                for (int q = lane; q < groups; q += kWave) {
-                    const uint32_t entry = queue[wave][q];
+                // Only a token whose bound (logit and gumbel_bound_of_word)
+                // reaches the best key known needs its logarithm pair: one or
+                // two passes in a wave's first trips, then hardly any.
+                for (int q0 = 0; q0 < groups; q0 += kWave) {  // wave-uniform trip count
+                    const uint32_t entry = q0 + lane < groups ? queue[wave][q0 + lane] : 0u;
                     const uint32_t g = entry >> 4;
-                    const uint32_t bitsg = entry & 0xFu;
-                    // the logits first: their load is in flight during the Philox rounds
-                    const uint4 xs = group_logits<DT>(row, aligned, g, bitsg, V);
+                    uint32_t left = entry & 0xFu;
+                    // the logits first: their load is in flight during the
+                    // Philox rounds (a lane without a group reads group 0)
+                    const GroupWords<DT> raw = load_group<DT>(row, g, V);
+                    const uint32_t seen = __hip_atomic_load(&block_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                     const uint4 rnd = philox4x32_10(g, (uint32_t)b, off_lo, off_hi, seed_lo, seed_hi);
-                    // one guarded pass per position of the group (a pass runs
-                    // when any lane of the wave has that token allowed): the
-                    // logit and the Philox word are then fixed registers
-                    auto noise = [&](uint32_t x, uint32_t word, uint32_t e) {
-                        const uint32_t i = g * 4u + e;
-                        const float key = __builtin_fmaf(__uint_as_float(x), inv_t, gumbel_of_word(word));
-                        const uint64_t packed =
-                            ((uint64_t)order_key(key) << 32) | (uint64_t)(0xFFFFFFFFu - i);
-                        best = max_u64(best, packed);
-                    };
-                    if (bitsg & 1u)
-                        noise(xs.x, rnd.x, 0u);
-                    if (bitsg & 2u)
-                        noise(xs.y, rnd.y, 1u);
-                    if (bitsg & 4u)
-                        noise(xs.z, rnd.z, 2u);
-                    if (bitsg & 8u)
-                        noise(xs.w, rnd.w, 3u);
+                    const uint32_t noise[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
+                    uint32_t x[4];
+                    group_values<DT>(raw, g, V, x);
+                    const uint32_t others = __builtin_amdgcn_readfirstlane(seen);
+                    wave_key = others > wave_key ? others : wave_key;
+                    float floor = key_value(wave_key);
+                    float bound[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        bound[e] = __builtin_fmaf(__uint_as_float(x[e]), inv_t, gumbel_bound_of_word(noise[e]));
+                        left &= bound[e] < floor ? ~(1u << e) : ~0u;
+                    }
+                    if (__ballot(left != 0)) {
+                        do {
+                            // each lane's highest bound first: the others seldom need their noise then
+                            uint32_t pick = 0, px = 0, pw = 0;
+                            float pb = -__builtin_inff();
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if ((left & (1u << e)) && !(bound[e] < pb)) {
+                                    pick = (uint32_t)e;
+                                    px = x[e];
+                                    pw = noise[e];
+                                    pb = bound[e];
+                                }
+                            if (left) {
+                                const float key = __builtin_fmaf(__uint_as_float(px), inv_t, gumbel_of_word(pw));
+                                const uint32_t i = g * 4u + pick;
+                                best = max_u64(best, (uint64_t)order_key(key) << 32 | (uint64_t)(0xFFFFFFFFu - i));
+                                left &= ~(1u << pick);
+                            }
+                            const uint32_t k = wave_reduce<true>((uint32_t)(best >> 32));
+                            wave_key = k > wave_key ? k : wave_key;
+                            floor = key_value(wave_key);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                left &= bound[e] < floor ? ~(1u << e) : ~0u;
+                        } while (__ballot(left != 0));
+                        if (lane == 0 && wave_key > others)
+                            (void)__hip_atomic_fetch_max(&block_key, wave_key, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
                 }
             }
             wave_lds_sync();  // every lane has read its entries before the next iteration writes

@@ -153,12 +153,14 @@ def step_bytes(w, logit_bytes, live_rows, B):
 
 
 def align_walk_kind(trans):
-    """Which walk dv_align runs for this table (the library decides on the
-    device from the same quantities): the whole compacted table staged in
-    LDS, the prefix-table walk (at most 98 compacted columns), or the tile
+    """Which walk dv_align runs for this table (the library decides from the
+    same quantities): the direct walk (at most 255 states), the whole
+    compacted table staged in LDS, the prefix-table walk (at most 98 compacted columns), or the tile
     walk.  Reporting only: it names the kernel the roofline figures cover."""
     import numpy as np
     S = trans.shape[0]
+    if S <= 255:
+        return "walk_direct_kernel"
     C = int(((trans >= 0) & (trans < S)).any(axis=0).sum())
     Cp = (C + 2) & ~1 if C < 256 else 256
     lds_table = 16 * 256 * 2

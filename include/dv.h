@@ -179,8 +179,9 @@ DV_API dv_status dv_validate_vocab(const int32_t *offsets, int32_t num_tokens, i
  * split over several blocks, they meet there (up to four blocks per row in
  * pairs, one 64-bit word per pair; more through a running maximum and an
  * arrival count per row; the block that finishes the row writes its
- * outputs and puts its words back to zero).  Returns 0 when a size is
- * outside its limit.
+ * outputs and puts its words back to zero).  For one num_tokens the size
+ * never falls as batch grows: a workspace made for a batch serves every
+ * smaller one.  Returns 0 when a size is outside its limit.
  */
 DV_API size_t dv_masked_step_workspace_bytes(int32_t batch, int32_t num_tokens);
 
@@ -279,8 +280,8 @@ DV_API dv_status dv_masked_step_opportunistic(const int32_t *next_state, const u
 
 /*
  * dv_masked_sample_workspace_bytes -- device workspace dv_masked_sample needs
- * for `batch` rows of `num_tokens` logits.  Returns 0 when a size is outside
- * its limit.
+ * for `batch` rows of `num_tokens` logits; for one num_tokens it never falls
+ * as batch grows.  Returns 0 when a size is outside its limit.
  */
 DV_API size_t dv_masked_sample_workspace_bytes(int32_t batch, int32_t num_tokens);
 

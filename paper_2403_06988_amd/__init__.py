@@ -292,8 +292,8 @@ def masked_sample_workspace_bytes(batch: int, num_tokens: int) -> int:
 
 
 def sample_workspace(batch: int, num_tokens: int, device) -> torch.Tensor:
-    """A zero-filled workspace for ``masked_sample`` (left zero by every call;
-    reusable by calls ordered on one stream)."""
+    """A zero-filled workspace for ``masked_sample`` with up to ``batch`` rows
+    (left zero by every call; reusable by calls ordered on one stream)."""
     n = masked_sample_workspace_bytes(batch, num_tokens)
     return torch.zeros(max(n, 1), dtype=torch.uint8, device=device)
 

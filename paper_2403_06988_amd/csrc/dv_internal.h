@@ -173,6 +173,18 @@ constexpr size_t row_meet_bytes(int B, int nchunks)
     return pairs > row_meet_bytes(B) ? pairs : row_meet_bytes(B);
 }
 
+// The bytes a query returns for a launch of B rows in nchunks chunks whose rows
+// may meet in pairs at any batch below `split_below`: room for three pair words
+// in each of those rows too, so that the size never falls as B grows and a
+// workspace made for B rows serves every smaller batch (the chunks per row,
+// and with them the words, rise again as the batch shrinks).
+constexpr size_t row_meet_bytes_upto(int B, int nchunks, int split_below)
+{
+    const int rows = B < 1 ? 1 : B < split_below ? B : split_below - 1;
+    const size_t pairs = align_up((size_t)rows * (kMeetTreeChunks - 1) * 8, 256);
+    return pairs > row_meet_bytes(B, nchunks) ? pairs : row_meet_bytes(B, nchunks);
+}
+
 struct RowMeet {
     uint64_t *best;
     uint32_t *arrived;
@@ -310,11 +322,12 @@ inline StepGeometry step_geometry(int B, int V, int dtype)
     return {chunk_vec, nchunks, threads};
 }
 
-// either dtype's launch shape
+// either dtype's launch shape (from kStepOneBlockRows rows on, the chunks per
+// row depend on V alone)
 inline size_t step_workspace_bytes(int B, int V)
 {
-    const size_t a = row_meet_bytes(B, step_geometry(B, V, 0).nchunks);
-    const size_t b = row_meet_bytes(B, step_geometry(B, V, 1).nchunks);
+    const size_t a = row_meet_bytes_upto(B, step_geometry(B, V, 0).nchunks, kStepOneBlockRows);
+    const size_t b = row_meet_bytes_upto(B, step_geometry(B, V, 1).nchunks, kStepOneBlockRows);
     return a > b ? a : b;
 }
 

@@ -469,7 +469,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_num_sgpr(80))) void 
 
 size_t sample_workspace_bytes(int B, int V)
 {
-    return row_meet_bytes(B, sample_geometry(B, V).nchunks);
+    return row_meet_bytes_upto(B, sample_geometry(B, V).nchunks, kOneBlockRows);
 }
 
 hipError_t launch_masked_sample(const int32_t *next_state, const uint32_t *allow, int S, int V,

@@ -64,6 +64,19 @@ struct SampleGeometry {
 SampleGeometry sample_geometry(int B, int V)
 {
     if (B >= kOneBlockRows) {
+        // Rows that fill at most half of the 1,024 lanes with allow words take
+        // 256 of them (half a word each up to 4,096 tokens): every wave that
+        // finds no word still costs its start, the block's barriers and a
+        // place on its compute unit.  us per step in 1,024 lanes and now, a
+        // twentieth and all of the tokens allowed: 1,024 x 1,000 8.5 and 6.7,
+        // 16.9 and 7.9; 2,048 x 4,096 15.6 and 8.1, 48.5 and 15.4; 2,048 x
+        // 16,384 20.2 and 14.3, 45.8 and 36.6; 1,024 x 20,000 12.9 and 11.2,
+        // 27.8 and 28.7; 1,024 x 32,000 15.5 and 14.6, 33.8 and 40.2.
+        if (V <= kRowThreads * 16) {
+            const int span = V <= kThreads * 16 ? 16 : 32;
+            const int iter = kThreads * span;
+            return {kThreads, (V + iter - 1) / iter * iter, 1, span};
+        }
         const int per_iter = kRowThreads * 32;
         return {kRowThreads, (V + per_iter - 1) / per_iter * per_iter, 1, 32};
     }

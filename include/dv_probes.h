@@ -86,6 +86,13 @@ DVPROBE_API int32_t dvprobe_step_floor(int32_t mode, const void *logits, int32_t
                                        int32_t *new_state, uint32_t *sink, int64_t sink_words,
                                        void *stream);
 
+/* The launch shape of the masked step (host only, no HIP call): `batch` rows of
+ * `num_tokens` logits of `dtype` (dv_dtype) are split into *chunks blocks a row
+ * of *lanes lanes, each taking *chunk_vectors 16-byte vectors.  Returns 0, or 1
+ * for a bad argument. */
+DVPROBE_API int32_t dvprobe_step_shape(int32_t batch, int32_t num_tokens, int32_t dtype, int32_t *chunk_vectors,
+                                       int32_t *chunks, int32_t *lanes);
+
 #ifdef __cplusplus
 }
 #endif

@@ -245,7 +245,13 @@ __device__ __forceinline__ bool meet_row(RowMeet m, int b, int c, int nchunks, u
 //
 // A row of V logits is split into `nchunks` chunks of `chunk_vec` 16-byte
 // vectors, one block of `threads` lanes each; with more than one chunk the
-// blocks meet in the workspace (above).  Blocks have 512 lanes.  A row is one
+// blocks meet in the workspace (above).  Blocks have 512 lanes, or 256 for fp32
+// rows of at most 1,024 vectors from 1,024 rows on: a block per row then has
+// little to stream, and its lanes without a vector still cost their start and
+// the block's meeting (us per step in 256-lane blocks of an earlier kernel, in
+// 512 and now, a twentieth of the tokens allowed: 8,192 rows x 1,000 28.0, 30.4
+// and 17.0; 8,192 x 1,001, rows off a 16-byte boundary, 29.0, 34.8 and 20.0;
+// 2,048 x 4,096 14.0, 11.7 and 10.0).  A row is one
 // block once B >= kStepOneBlockRows (a block per compute unit already) or when
 // it holds at most kStepSingleBlockBatches batches (1,024 vectors each: the
 // meeting costs more than the second block's stream saves at any B: V =
@@ -255,6 +261,9 @@ __device__ __forceinline__ bool meet_row(RowMeet m, int b, int c, int nchunks, u
 // Otherwise as many chunks as step_geometry's rule gives.
 constexpr int kStepOneBlockRows = 256;
 constexpr int kStepThreads = 512;
+constexpr int kStepFewThreads = 256;
+constexpr int kStepFewThreadsRows = 1024;
+constexpr int kStepFewThreadsVec = 1024;
 constexpr int kStepStageWords = 8192;    // mask words a bf16 block may stage in LDS
 constexpr int kStepMaxChunkVec = (kStepStageWords - 1) * 4 / kStepThreads * kStepThreads;
 constexpr int kStepSingleBlockBatches = 3;
@@ -274,6 +283,8 @@ inline StepGeometry step_geometry(int B, int V, int dtype)
     const int nvec = V / vec;
     const int batches = (nvec + 2 * threads - 1) / (2 * threads);  // of two vectors per lane
     const int b = B > 0 ? B : 1;
+    if (!bf16 && b >= kStepFewThreadsRows && nvec <= kStepFewThreadsVec)
+        return {kStepFewThreadsVec, 1, kStepFewThreads};
     int want;
     if (b >= kStepOneBlockRows || batches <= kStepSingleBlockBatches) {
         want = 1;

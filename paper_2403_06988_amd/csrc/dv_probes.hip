@@ -411,4 +411,16 @@ int32_t dvprobe_lds_gather(const uint32_t *table, int32_t table_entries, int32_t
                                    static_cast<hipStream_t>(stream)) == hipSuccess ? 0 : 6;
 }
 
+int32_t dvprobe_step_shape(int32_t batch, int32_t num_tokens, int32_t dtype, int32_t *chunk_vectors, int32_t *chunks,
+                           int32_t *lanes)
+{
+    if (batch < 0 || num_tokens < 1 || (dtype != 0 && dtype != 1) || !chunk_vectors || !chunks || !lanes)
+        return 1;
+    const dv::StepGeometry g = dv::step_geometry(batch, num_tokens, dtype);
+    *chunk_vectors = g.chunk_vec;
+    *chunks = g.nchunks;
+    *lanes = g.threads;
+    return 0;
+}
+
 }  // extern "C"

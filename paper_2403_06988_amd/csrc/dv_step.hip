@@ -1062,17 +1062,21 @@ hipError_t launch_masked_rows(const int32_t *next_state, const uint32_t *allow, 
     if (dtype == 0) {
         const bool aligned = map.rows_aligned(logits, 4);
         const bool ahead2 = g.chunk_vec >= kAhead2MinVec;
-#define DV_STEP_F32(A, A2)                                                                                     \
-    masked_step_kernel<kThreads, kU, A, A2><<<grid, kThreads, 0, stream>>>(                                    \
+#define DV_STEP_F32(T, A, A2)                                                                                  \
+    masked_step_kernel<T, kU, A, A2><<<grid, T, 0, stream>>>(                                                  \
         next_state, allow, S, V, W, states, logits, map, g.chunk_vec, g.nchunks, token, new_state, meet)
-        if (aligned && ahead2)
-            DV_STEP_F32(false, true);
+        if (g.threads == kStepFewThreads && aligned)
+            DV_STEP_F32(kStepFewThreads, false, false);
+        else if (g.threads == kStepFewThreads)
+            DV_STEP_F32(kStepFewThreads, true, false);
+        else if (aligned && ahead2)
+            DV_STEP_F32(kThreads, false, true);
         else if (aligned)
-            DV_STEP_F32(false, false);
+            DV_STEP_F32(kThreads, false, false);
         else if (ahead2)
-            DV_STEP_F32(true, true);
+            DV_STEP_F32(kThreads, true, true);
         else
-            DV_STEP_F32(true, false);
+            DV_STEP_F32(kThreads, true, false);
 #undef DV_STEP_F32
     } else {
         const bool aligned = map.rows_aligned(logits, 2);

@@ -257,7 +257,7 @@ __device__ __forceinline__ bool meet_row(RowMeet m, int b, int c, int nchunks, u
 // meeting costs more than the second block's stream saves at any B: V =
 // 16,000 bf16 in 1 and 2 chunks, us per step: B = 1 3.48 and 4.04, B = 128
 // 4.54 and 4.90; V = 24,000: B = 1 3.93 and 4.40, B = 64 4.97 and 5.05; at
-// four batches, V = 28,000 and 32,000, two chunks win from B = 2 to 64).
+// four batches two chunks win up to B = 127).
 // Otherwise as many chunks as step_geometry's rule gives.
 constexpr int kStepOneBlockRows = 256;
 constexpr int kStepThreads = 512;
@@ -309,14 +309,15 @@ inline StepGeometry step_geometry(int B, int V, int dtype)
             ++r;  // ceil(sqrt(B))
         want = (32 * r + b / 2) / b;
     }
-    // Rows of four batches meet in pairs at most, and at the ends of the
-    // range hardly split (V = 32,000 bf16, us per step: B = 1 in 1 4.23, in 2
-    // 4.31, in more 4.5; B = 2 in 2 4.29, in 4 4.50; B = 8 in 2 4.82, in 4
-    // 4.73; B = 64 in 1 5.33, in 2 5.21; B = 128 in 1 5.54, in 2 5.59).
-    if (batches <= 4) {
-        const int few = b == 1 || b >= 128 ? 1 : b < 4 ? 2 : 4;
-        want = want < few ? want : few;
-    }
+    // Rows of four batches in two chunks of two (what 256 / B leaves from 128
+    // rows on is one or two anyway).  Us per step in 1, 2, 3, 4 and 6 chunks:
+    // bf16 V = 32,000 B = 1 5.22, 5.18, 5.61, 5.19, 5.09, B = 8 5.71, 5.48,
+    // 5.82, 5.41, 5.40, B = 64 5.97, 5.80, 6.22, 5.83, 5.90, B = 70 5.95, 5.84,
+    // 6.27, 6.69, 6.67; V = 25,000 B = 8 5.26, 5.08, 5.64, 5.18, 5.28, B = 70
+    // 5.82, 5.65, 6.23, 6.61, 6.46; fp32 V = 16,000 B = 8 5.47, 5.25, 5.61,
+    // 5.32, 5.38, B = 70 5.83, 5.72, 6.13, 6.13, 6.22.
+    if (batches <= 4)
+        want = want < 2 ? want : 2;
     // at least one vector per lane per chunk
     const int max_chunks = nvec / threads > 1 ? nvec / threads : 1;
     want = want > max_chunks ? max_chunks : want;

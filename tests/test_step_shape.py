@@ -77,3 +77,9 @@ def test_short_fp32_rows(V, pad):
         want = oracle.spec_verify(ns, al, states[:b], props, to_oracle(pos))
         for g, w in zip(got, want):
             np.testing.assert_array_equal(g.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("dtype,V", [(BF16, 24584), (BF16, 32000), (BF16, 32768), (F32, 12292), (F32, 16384)])
+def test_rows_of_four_batches_take_two_chunks_at_most(dtype, V):
+    for B in range(1, 256):
+        assert step_shape(B, V, dtype)[1] == (2 if B <= 128 else 1), B

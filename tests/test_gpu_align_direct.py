@@ -51,6 +51,27 @@ def test_direct_walk(S, V, dead):
         assert np.array_equal(al.cpu().numpy().view(np.uint32), al_o)
 
 
+@pytest.mark.parametrize("S", [1, 17, 255])
+@pytest.mark.parametrize("last", [8, 9, 16, 17, 3001])
+def test_direct_walk_long_tokens(S, last):
+    """Tokens of many words of 8 bytes, which are read a word ahead of the walk,
+    that live to their end; the last one ends the byte array."""
+    import paper_2403_06988_amd as dv
+
+    rng = np.random.default_rng(S + last)
+    trans = rng.integers(0, S, (S, 256)).astype(np.int32)
+    trans[rng.random((S, 256)) < 0.002] = -1
+    lens = np.array([1, 3000, 0, 7, 64, 65, 63, 255, 256, 257, 1023, 8, 24, 40, 2, last])
+    offsets = np.zeros(len(lens) + 1, np.int32)
+    offsets[1:] = np.cumsum(lens)
+    data = rng.integers(0, 256, int(offsets[-1])).astype(np.uint8)
+    ns, al = dv.align(torch.from_numpy(trans).to(DEV), torch.from_numpy(offsets).to(DEV),
+                      torch.from_numpy(data).to(DEV))
+    ns_o, al_o = oracle.align(trans, offsets, data)
+    assert np.array_equal(ns.cpu().numpy(), ns_o)
+    assert np.array_equal(al.cpu().numpy().view(np.uint32), al_o)
+
+
 def test_direct_walk_decreasing_offsets_read_as_empty():
     import paper_2403_06988_amd as dv
 

@@ -246,12 +246,13 @@ __device__ __forceinline__ bool meet_row(RowMeet m, int b, int c, int nchunks, u
 // A row of V logits is split into `nchunks` chunks of `chunk_vec` 16-byte
 // vectors, one block of `threads` lanes each; with more than one chunk the
 // blocks meet in the workspace (above).  Blocks have 512 lanes, or 256 for fp32
-// rows of at most 1,024 vectors from 1,024 rows on: a block per row then has
-// little to stream, and its lanes without a vector still cost their start and
-// the block's meeting (us per step in 256-lane blocks of an earlier kernel, in
-// 512 and now, a twentieth of the tokens allowed: 8,192 rows x 1,000 28.0, 30.4
-// and 17.0; 8,192 x 1,001, rows off a 16-byte boundary, 29.0, 34.8 and 20.0;
-// 2,048 x 4,096 14.0, 11.7 and 10.0).  A row is one
+// rows of at most 1,024 vectors once a compute unit has more than one: a block
+// has little to stream then, and its lanes without a vector still cost their
+// start and the block's meeting (us per step in 256-lane blocks of an earlier
+// kernel, in 512 and now, a twentieth of the tokens allowed: 8,192 rows x 1,000
+// 28.0, 30.4 and 17.0; 8,192 x 1,001, rows off a 16-byte boundary, 29.0, 34.8
+// and 20.0; 2,048 x 4,096 14.0, 11.7 and 10.0; in 512 and now 300 x 1,000 4.56
+// and 4.10, 256 x 4,001 4.48 and 4.59).  A row is one
 // block once B >= kStepOneBlockRows (a block per compute unit already) or when
 // it holds at most kStepSingleBlockBatches batches (1,024 vectors each: the
 // meeting costs more than the second block's stream saves at any B: V =
@@ -262,7 +263,6 @@ __device__ __forceinline__ bool meet_row(RowMeet m, int b, int c, int nchunks, u
 constexpr int kStepOneBlockRows = 256;
 constexpr int kStepThreads = 512;
 constexpr int kStepFewThreads = 256;
-constexpr int kStepFewThreadsRows = 1024;
 constexpr int kStepFewThreadsVec = 1024;
 constexpr int kStepStageWords = 8192;    // mask words a bf16 block may stage in LDS
 constexpr int kStepMaxChunkVec = (kStepStageWords - 1) * 4 / kStepThreads * kStepThreads;
@@ -283,7 +283,7 @@ inline StepGeometry step_geometry(int B, int V, int dtype)
     const int nvec = V / vec;
     const int batches = (nvec + 2 * threads - 1) / (2 * threads);  // of two vectors per lane
     const int b = B > 0 ? B : 1;
-    if (!bf16 && b >= kStepFewThreadsRows && nvec <= kStepFewThreadsVec)
+    if (!bf16 && b > kStepOneBlockRows && nvec <= kStepFewThreadsVec)
         return {kStepFewThreadsVec, 1, kStepFewThreads};
     int want;
     if (b >= kStepOneBlockRows || batches <= kStepSingleBlockBatches) {

@@ -16,6 +16,7 @@ import torch
 import oracle
 import workloads as W
 from tests.gpu_common import run_chain, to_oracle, u32
+from tests.test_step_shape import BF16, F32, step_shape
 
 pytestmark = pytest.mark.gpu
 
@@ -180,9 +181,9 @@ def test_align_all_transitions_dead(dv):
 
 @pytest.mark.parametrize("dead_byte", [None, 0xFF, 0x00, 0x80])
 def test_align_every_byte_value(dv, dead_byte):
-    """All 256 bytes live (C = 256 classes, no spare class for dead bytes), or
-    all but one (C = 255: the dead byte's class is the last one).  Every
-    single-byte token and tokens through the dead byte are walked."""
+    """All 256 bytes live, or all but one.  Every single-byte token and tokens
+    through the dead byte are walked (50 states: the direct walk;
+    test_gpu_align_pipeline.py has the same for the class pipeline)."""
     rng = np.random.default_rng(5)
     S = 50
     trans = rng.integers(0, S, size=(S, 256)).astype(np.int32)
@@ -1233,8 +1234,14 @@ def test_split_rows_every_meeting_form_one_workspace(dv):
              ("step", torch.bfloat16, 128, 128256), ("step", torch.bfloat16, 33, 128256),
              ("step", torch.float32, 64, 70001), ("step", torch.float32, 100, 70001),
              ("step", torch.float32, 150, 40000), ("step", torch.float32, 20, 70001),
+             ("step", torch.bfloat16, 70, 128256), ("step", torch.float32, 70, 70001),
+             ("step", torch.bfloat16, 8, 128256), ("step", torch.float32, 9, 70007),
              ("sample", torch.bfloat16, 512, 32000), ("sample", torch.bfloat16, 700, 32000),
              ("sample", torch.float32, 1000, 32000), ("sample", torch.bfloat16, 256, 32000)]
+    # the greedy calls take every form in both dtypes: 2, 3 and 4 chunks a row, and more
+    for dtype, code in ((torch.float32, F32), (torch.bfloat16, BF16)):
+        forms = {min(5, step_shape(B, V, code)[1]) for k, d, B, V in calls if k == "step" and d == dtype}
+        assert forms >= {2, 3, 4, 5}, (dtype, forms)
     need = max(dv.masked_step_workspace_bytes(B, V) if k == "step" else dv.masked_sample_workspace_bytes(B, V)
                for k, _, B, V in calls)
     ws = torch.zeros(need, dtype=torch.uint8, device=DEV)

@@ -31,7 +31,7 @@ def _table(rng, S, V):
 @pytest.mark.parametrize("B,V", [
     (1, 3), (2, 4), (3, 4095), (2, 4101), (5, 8197),
     (256, 32764), (257, 32768), (256, 32773),        # one chunk a row, at the skipping threshold
-    (128, 65532), (130, 65541), (64, 131079),        # two and four chunks
+    (128, 65532), (130, 65541), (64, 131079),        # two, one and four chunks
     (9, 70007), (1, 262151),                         # many chunks
 ])
 def test_f32_step_edges(B, V):

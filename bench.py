@@ -155,17 +155,16 @@ def step_bytes(w, logit_bytes, live_rows, B):
 def align_walk_kind(trans):
     """Which walk dv_align runs for this table (the library decides from the
     same quantities): the direct walk (at most 255 states), the whole
-    compacted table staged in LDS, the prefix-table walk (at most 98 compacted columns), or the tile
-    walk.  Reporting only: it names the kernel the roofline figures cover."""
+    compacted table staged in LDS, the prefix-table walk (at most 98 compacted
+    columns), or the tile walk.  Reporting only: it names the kernel the
+    roofline figures cover."""
     import numpy as np
     S = trans.shape[0]
     if S <= 255:
         return "walk_direct_kernel"
     C = int(((trans >= 0) & (trans < S)).any(axis=0).sum())
     Cp = (C + 2) & ~1 if C < 256 else 256
-    lds_table = 16 * 256 * 2
-    if S <= 512:
-        lds_table = max(lds_table, min(S * 256 * 2, 64 * 1024))
+    lds_table = 64 * 1024 if S <= 512 else 16 * 256 * 2
     if S * Cp * 2 <= lds_table:
         return "walk_kernel (whole table in LDS)"
     return "walk_prefix_kernel" if Cp <= 98 else "walk_kernel"
@@ -703,12 +702,20 @@ def bench_opportunistic(dv, w, ns, al, x, tokens_all, states_all, dev, adherent=
     a fraction ``adherent`` of the row-steps favour the chain's own (allowed)
     choice -- raising the chosen logit leaves the chain unchanged.  With every
     row-step adherent no row is read twice: the time is that of the
-    unconstrained greedy pass alone.  Each chain
-    is captured as a HIP graph and replayed; the check's hit rate is the
-    fraction of live row-steps whose overall argmax is allowed."""
+    unconstrained greedy pass alone.  The library makes the check where one
+    block covers a row of a large enough batch; elsewhere the call is the
+    masked step itself, and so is the time (``checked_first``).  Each chain is
+    captured as a HIP graph and replayed; the check's hit rate is the fraction
+    of live row-steps whose overall argmax is allowed."""
+    import ctypes
+
     import numpy as np
     import torch
 
+    shape = [ctypes.c_int32() for _ in range(3)]
+    if probe_lib().dvprobe_step_shape(w.B, w.V, 1, *[ctypes.byref(v) for v in shape]):
+        raise SystemExit("dvprobe_step_shape failed")
+    checked_first = shape[1].value == 1 and (w.B >= 256 or (w.B >= 64 and w.V <= 32768))
     steps = tokens_all.shape[0]
     ws = dv.step_workspace(w.B, w.V, dev)
     sts = torch.empty_like(states_all)
@@ -743,7 +750,7 @@ def bench_opportunistic(dv, w, ns, al, x, tokens_all, states_all, dev, adherent=
         return {"us_per_step": float(np.median(times)) * 1e6, "matches_masked_step": same,
                 "check_hit_rate": float(hit.sum()) / max(int(live.sum()), 1)}
 
-    out = {"random_logits": timed_chain(x)}
+    out = {"checked_first": checked_first, "random_logits": timed_chain(x)}
     g = torch.Generator(device=dev)
     g.manual_seed(7)
     u = torch.rand(tokens_all.shape, generator=g, device=dev)

@@ -84,7 +84,6 @@ constexpr int kDirectG = 16;
 constexpr int kDirectThreads = 1024;
 constexpr int kDirectFewThreads = 256;    // where tiles of 1,024 tokens would leave compute units idle
 constexpr int kDirectTargetBlocks = 512;  // two resident blocks of 1,024 lanes per compute unit
-constexpr int kDirectLdsMax = (kDirectStates + 1) * 256;
 
 // token lengths with a special meaning in the walk
 constexpr int kPastEnd = -1;  // a lane slot past the last token: never stored
@@ -724,11 +723,7 @@ hipError_t launch_walk_direct(const int32_t *trans, int S, const int32_t *offset
                               const uint8_t *accepting, int eos_token, int32_t *next_state, uint32_t *allow,
                               hipStream_t stream)
 {
-    // LDS beyond the default 64 KB per block must be opted into once.
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(walk_direct_kernel<THREADS>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kDirectLdsMax);
-    if (attr != hipSuccess)
-        return attr;
+    static_assert((kDirectStates + 1) * 256 <= 64 * 1024, "the default limit of a block's LDS");
     // A block keeps its table for as many state groups as leave
     // kDirectTargetBlocks blocks, which covers the table's loads.
     const long long nt = (V + THREADS - 1) / THREADS, ng = (S + kDirectG - 1) / kDirectG;
@@ -776,8 +771,10 @@ hipError_t launch_align(const int32_t *trans, int S, const int32_t *offsets, con
     if (S <= kDirectStates) {
         // Fewer tiles than compute units: a quarter of the tokens per block
         // fills them.  Above that the wide blocks win, since the narrow ones
-        // copy the table four times as often (250 states x 32,000 tokens, at 8
-        // states a group: 25 us in 1,024-lane blocks, 50 in 256-lane ones).
+        // copy the table four times as often (32,000 tokens, us in 1,024-lane
+        // and 256-lane blocks: 250 states, 512 tiles, 22.5 and 39.0; 128
+        // states, 256 tiles, 14.1 and 15.5; 64 states, 128 tiles, 12.5 and
+        // 11.0).
         const long long tiles = (long long)((V + kDirectThreads - 1) / kDirectThreads) *
                                 ((S + kDirectG - 1) / kDirectG);
         return tiles < kDirectTargetBlocks / 2
@@ -794,17 +791,11 @@ hipError_t launch_align(const int32_t *trans, int S, const int32_t *offsets, con
     const int W = (V + 31) / 32;
 
     // LDS for the table.  The column count C is only known on the device, so
-    // for small S the launch reserves up to kWholeLdsMax bytes and the kernel
+    // up to 512 states the launch reserves kWholeLdsMax bytes and the kernel
     // stages the whole table when S * Cp * 2 fits; otherwise (and always for
     // S > 512, where a whole table would leave too little LDS for occupancy)
     // it stages only the block's row tile.
-    int lds_table = kRowsLds;
-    if (S <= 512) {
-        const size_t whole_worst = (size_t)S * 256 * 2;
-        lds_table = (int)(whole_worst < (size_t)kWholeLdsMax ? whole_worst : (size_t)kWholeLdsMax);
-        if (lds_table < kRowsLds)
-            lds_table = kRowsLds;
-    }
+    const int lds_table = S <= 512 ? kWholeLdsMax : kRowsLds;
 
     // LDS beyond the default 64 KB per block must be opted into once.
     static const hipError_t lds_attr = hipFuncSetAttribute(

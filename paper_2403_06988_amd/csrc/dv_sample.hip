@@ -21,13 +21,14 @@
 // Of a dense wave's tokens that leaves one or two passes in its first trips
 // and hardly any later: us per step with a pair for every token and now, three
 // fifths of the tokens allowed: 256 x 128,256 59.4 and 35.7, 64 x 32,000 10.7
-// and 9.3, 1,024 x 16,000 35.7 and 24.2, 8 x 128,256 10.7 and 9.1; rows that
-// start at any alignment, 100 x 50,257, 20.6 and 13.0.  Where a wave's allowed tokens are hardly more than its
-// groups (sparse masks) it queues single tokens instead, so that no lane
-// waits on a neighbour's second logarithm pair; dense masks keep the groups
-// and so one Philox call per 4 tokens.  Lanes combine exact
-// (order-preserving fp32 key << 32 | ~index) maxima, so ties go to the lowest
-// index and the result does not depend on the order of the work.
+// and 9.3, 1,024 x 16,000 36.9 and 23.1, 8 x 128,256 10.7 and 9.1; rows that
+// start at any alignment, 100 x 50,257, 20.6 and 13.0.  Where a wave's allowed
+// tokens are hardly more than its groups (sparse masks) it queues single
+// tokens instead, so that no lane waits on a neighbour's second logarithm
+// pair; dense masks keep the groups and so one Philox call per 4 tokens.
+// Lanes combine exact (order-preserving fp32 key << 32 | ~index) maxima, so
+// ties go to the lowest index and the result does not depend on the order of
+// the work.
 #include "dv_sample.h"
 
 namespace dv {
@@ -303,8 +304,9 @@ __device__ __forceinline__ void group_values(GroupWords<DT> v, uint32_t g, int V
 // lane 31 into the upper two rows.  Two small counts share a word, so one scan
 // serves both: six adds and no scalar registers, where the ballots of the
 // counts' bits took about fifty instructions and twenty scalar registers (us
-// per step with those and now, a twentieth of the tokens allowed: 256 x 128,256
-// 20.3 and 19.7, 8 x 32,000 5.43 and 5.33, 1,024 x 32,000 22.4 and 22.0).
+// per step with those and now, timed in turn: a twentieth of the tokens allowed
+// 256 x 128,256 17.8 and 17.1, 8 x 32,000 5.7 and 5.5, 1,024 x 32,000 17.2 and
+// 16.6; one in 500 256 x 128,256 12.1 and 11.2).
 // Every lane of the wave must be active.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)

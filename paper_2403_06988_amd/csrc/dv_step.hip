@@ -5,15 +5,16 @@
 // the design is about keeping enough bytes in flight and spending few ALU
 // operations per element.
 //   * Launch shape (step_geometry).  A row is one 512-lane block once B >=
-//     256 (every CU gets at least one row), or when the row holds at most
-//     three batches (24,576 bf16 logits; the meeting costs more than a second
-//     block saves).  Otherwise each row is split into chunks, one block each,
-//     never more than 256 in all, and the chunks meet in the workspace (meet_row): up
-//     to four chunks in pairs, each pair's second block learning both
-//     values from one device-scope atomic maximum (one round trip per
-//     level); more chunks through a device-scope atomic maximum and then an
-//     atomic count whose operand depends on the maximum's result, the block
-//     that counts last taking the row's result.  The finishing block puts
+//     256 (every CU gets at least one row; short fp32 rows take 256 lanes
+//     beyond that), or when the row holds at most three batches (24,576 bf16
+//     logits; the meeting costs more than a second block saves).  Otherwise
+//     each row is split into chunks, one block each, at most 256 in all, and
+//     the chunks meet in the workspace (meet_row): up to four chunks in
+//     pairs, each pair's second block learning both values from one
+//     device-scope atomic maximum (one round trip per level); more chunks
+//     through a device-scope atomic maximum and then an atomic count whose
+//     operand depends on the maximum's result, the block that counts last
+//     taking the row's result.  The finishing block puts
 //     the entries back to zero.  For bf16 the 64-bit entry also carries the
 //     winner's next state, so that block reads nothing more.  No second
 //     kernel and no device-wide fences (a release fence at device scope
@@ -26,15 +27,16 @@
 //     Rows that start on a 16-byte boundary are read as raw buffers whose
 //     records end at the chunk's end: one add per load for the address, and
 //     a lane past the chunk reads zeros (no clamp, no memory access).
-//   * Mask bytes (one per 8 logits).  With two or more blocks per compute
-//     unit, the block first copies its chunk's mask bytes into LDS; with one,
-//     chunks of at least 8 batches read each batch's mask bytes from memory
-//     two batches ahead of its logits.  Either way each later batch's
-//     offsets are chosen from them: a vector with no allowed token gets an
-//     offset past the buffer's records, which reads zeros without a memory
-//     access, so a 128-byte line with no allowed token is never fetched.
-//     Shorter chunks at one block per unit read their mask bytes beside
-//     their logits, and every line.
+//   * Mask bytes (one per 8 logits).  Chunks of at least 8 batches, at up to
+//     four blocks per compute unit (fp32: at any number), read each batch's
+//     mask bytes from memory two batches ahead of its logits; other bf16
+//     chunks, with two or more blocks per unit, first copy theirs into LDS.
+//     Either way each later batch's offsets are chosen from them: a vector
+//     with no allowed token gets an offset past the buffer's records, which
+//     reads zeros without a memory access, so a 128-byte line with no allowed
+//     token is never fetched.  The rest (shorter chunks, at one block per
+//     unit in bf16) read their mask bytes beside their logits, and every
+//     line.
 //   * bf16 arithmetic, a batch at a time in two parts.  Fold: per 32-bit
 //     word (two logits) a v_pk_ashrrev_i16 and two bit operations give the
 //     order-preserving 16-bit keys ANDed with two 16-bit lane masks (from an
@@ -45,7 +47,8 @@
 //     maximum search their masked keys for its lowest index.  The fast key
 //     differs from the exact ordering only for NaN (which must rank as -inf)
 //     and -0.0 (which must tie with +0.0); a batch whose maximum is one of
-//     those few key values is redone with exact keys.
+//     those few key values, or -inf's, is redone with exact keys unless the
+//     wave already holds a key that it cannot beat.
 //   * A row need not be 16-byte aligned (any row stride): the elements
 //     before its first 16-byte boundary are read one by one and the mask
 //     bits of each vector are taken from two mask bytes, shifted.  Such
@@ -241,8 +244,8 @@ __device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t v, bool is_max)
 //   pass 2: only if the batch beats the wave's best so far: lanes holding
 //           the maximum find its first position in their registers, and a
 //           wave-wide min picks the lowest index.  A batch whose maximum is
-//           one of the inexact fast keys (NaN, -0.0 / +0.0) is redone with
-//           exact keys.
+//           NaN, -inf or a zero is redone with exact keys, for -inf and the
+//           zeros only while the wave holds nothing as good.
 // The waves' results meet in one block-wide maximum at the end.  Without
 // the mask (MASKED false: the model's own choice, for opportunistic
 // masking) every element of the chunk counts as allowed and no mask byte is
@@ -395,18 +398,17 @@ __device__ __forceinline__ RowSplit split_row(const char *row, int V)
 // (wave-uniform).  The mask byte of vector v (bits 8v .. 8v + 7 of the
 // allow row) is mbytes[v - moff]: the allow row itself (moff = 0) or the
 // chunk's bytes staged in LDS.  `db` holds the second batch when STAGED
-// (issued by the caller before the staging finished).  SELECT (STAGED
-// only): vectors with no allowed token are not read (see
-// load_batch_buf_sel).  AHEAD2 (aligned rows streamed from memory): the
-// mask bytes are read two batches ahead of their logits and choose the
-// loads in the same way.
-template <int DT, int THREADS, int U, bool MASKED, bool SHIFTED, bool STAGED, bool SELECT, bool AHEAD2 = false>
+// (issued by the caller before the staging finished); vectors with no allowed
+// token are then not read from the third batch on (see load_batch_buf_sel).
+// AHEAD2 (mask bytes streamed from memory): they are read two batches ahead of
+// their logits and choose the loads in the same way.
+template <int DT, int THREADS, int U, bool MASKED, bool SHIFTED, bool STAGED, bool AHEAD2 = false>
 __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *arow, const uint8_t *mbytes,
                                               int moff, const int32_t *ns_row, RowSplit rs, int v0, int v1,
                                               bool first, bool last, int V, const uint4 *lut, uint4 (&da)[U],
                                               uint4 (&db)[U], uint64_t &vec_pack, int &vec_ns)
 {
-    static_assert(!SELECT || STAGED, "selection reads the staged mask bytes");
+    static_assert(!STAGED || MASKED, "the staged mask bytes choose the loads");
     static_assert(!AHEAD2 || (MASKED && !STAGED), "two batches ahead: the streamed mask bytes choose the loads");
     static_assert(DT == 1 || !STAGED, "the staged mask bytes hold one byte per bf16 vector");
     constexpr int kVec = Elt<DT>::kVec;
@@ -633,16 +635,10 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
         if constexpr (STAGED) {
             // Both first batches are in flight (issued by the caller) and the
             // mask bytes are in LDS: reading them costs no memory trip, so
-            // with SELECT every later batch's addresses are chosen from them.
+            // every later batch's addresses are chosen from them.
             // Each batch's mask bytes are read from LDS once, two batches
             // ahead, and serve both its addresses and its fold.
             const __amdgpu_buffer_rsrc_t rl = raw_buffer(vrow, (uint32_t)v1 * 16u);
-            auto issue = [&](uint4 (&d)[U], int vb, const uint32_t (&sel)[U]) {
-                if constexpr (SELECT && MASKED)
-                    load_batch_buf_sel<THREADS, U>(d, rl, vb, sel);
-                else
-                    load_batch<THREADS, U>(d, vrow, vb, v1);
-            };
             uint32_t na[U], nb[U];
             load_masks(ma, v0);
             live(ma, v0);
@@ -656,7 +652,7 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
                     uint32_t km[4 * U];
                     const uint32_t any = fold(da, la, ma, km);
                     __builtin_amdgcn_sched_barrier(0);
-                    issue(da, vb + 2 * kStep, na);
+                    load_batch_buf_sel<THREADS, U>(da, rl, vb + 2 * kStep, na);
                     __builtin_amdgcn_sched_barrier(0);
                     entries(lb, mb);
                     reduce(km, any, vb);
@@ -668,7 +664,7 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
                     const bool in = vb + kStep < v1;  // block-uniform
                     const uint32_t any = in ? fold(db, lb, mb, km) : 0u;
                     __builtin_amdgcn_sched_barrier(0);
-                    issue(db, vb + 3 * kStep, nb);
+                    load_batch_buf_sel<THREADS, U>(db, rl, vb + 3 * kStep, nb);
                     __builtin_amdgcn_sched_barrier(0);
                     entries(la, na);
                     if (in)
@@ -802,17 +798,17 @@ __device__ __forceinline__ uint64_t scan_rows(const char *row, const uint32_t *a
 // ANY_ALIGN false: the caller has checked that every row is 16-byte aligned,
 // so only the aligned scan is compiled (fewer registers: more resident
 // blocks where several share a CU).
-template <int DT, int THREADS, int U, bool MASKED, bool ANY_ALIGN, bool STAGED, bool SELECT, bool AHEAD2 = false>
+template <int DT, int THREADS, int U, bool MASKED, bool ANY_ALIGN, bool STAGED, bool AHEAD2 = false>
 __device__ __forceinline__ uint64_t scan_chunk(const char *row, const uint32_t *arow, const uint8_t *mbytes,
-                                                    int moff, const int32_t *ns_row, RowSplit rs, int v0, int v1,
-                                                    bool first, bool last, int V, const uint4 *lut, uint4 (&da)[U],
-                                                    uint4 (&db)[U], uint64_t &vec_pack, int &vec_ns)
+                                               int moff, const int32_t *ns_row, RowSplit rs, int v0, int v1,
+                                               bool first, bool last, int V, const uint4 *lut, uint4 (&da)[U],
+                                               uint4 (&db)[U], uint64_t &vec_pack, int &vec_ns)
 {
     if (!ANY_ALIGN || rs.head == 0)
-        return scan_rows<DT, THREADS, U, MASKED, false, STAGED, SELECT, AHEAD2>(
+        return scan_rows<DT, THREADS, U, MASKED, false, STAGED, AHEAD2>(
             row, arow, mbytes, moff, ns_row, rs, v0, v1, first, last, V, lut, da, db, vec_pack, vec_ns);
-    return scan_rows<DT, THREADS, U, MASKED, true, STAGED, SELECT, AHEAD2>(row, arow, mbytes, moff, ns_row, rs, v0, v1, first,
-                                                               last, V, lut, da, db, vec_pack, vec_ns);
+    return scan_rows<DT, THREADS, U, MASKED, true, STAGED, AHEAD2>(
+        row, arow, mbytes, moff, ns_row, rs, v0, v1, first, last, V, lut, da, db, vec_pack, vec_ns);
 }
 
 // Mask words staged per block: the chunk's mask bytes (one per vector, plus
@@ -886,7 +882,7 @@ __device__ __forceinline__ void masked_step_chunk(
                                       [&] { load_batch<THREADS, U>(db, vrow, v0 + THREADS * U, v1); });
             fill_lut(lut);
             lds_barrier();
-            mine = scan_chunk<DT, THREADS, U, true, ANY_ALIGN, true, true>(
+            mine = scan_chunk<DT, THREADS, U, true, ANY_ALIGN, true>(
                 row, arow, reinterpret_cast<const uint8_t *>(staged), v0, next_state + (size_t)s * V, rs, v0, v1,
                 c == 0, c == nchunks - 1, V, lut, da, db, vec_pack, vec_ns);
         } else if (live) {  // no whole vector in this chunk: the head and tail elements only
@@ -906,7 +902,7 @@ __device__ __forceinline__ void masked_step_chunk(
             lds_barrier();
         }
         if (live)
-            mine = scan_chunk<DT, THREADS, U, true, ANY_ALIGN, false, false, AHEAD2>(
+            mine = scan_chunk<DT, THREADS, U, true, ANY_ALIGN, false, AHEAD2>(
                 row, arow, reinterpret_cast<const uint8_t *>(arow), 0, next_state + (size_t)s * V, rs, v0, v1,
                 c == 0, c == nchunks - 1, V, lut, da, db, vec_pack, vec_ns);
     }
@@ -995,7 +991,7 @@ __global__ __launch_bounds__(THREADS) void opportunistic_step_bf16_kernel(
     uint64_t mine = 0, vec_pack = 0;
     int vec_ns = kNsUnknown, ns;
     if (live)
-        mine = scan_chunk<1, THREADS, U, false, ANY_ALIGN, false, false>(
+        mine = scan_chunk<1, THREADS, U, false, ANY_ALIGN, false>(
             row, arow, reinterpret_cast<const uint8_t *>(arow), 0, ns_row, rs, 0, rs.nvec, true, true, V, lut, da, db,
             vec_pack, vec_ns);
     uint64_t best = block_max_ns<THREADS>(mine, vec_pack, vec_ns, ns);
@@ -1008,7 +1004,7 @@ __global__ __launch_bounds__(THREADS) void opportunistic_step_bf16_kernel(
     if (miss) {  // block-uniform
         if (rs.nvec > 0)
             load_batch<THREADS, U>(da, row + 2 * rs.head, 0, rs.nvec);
-        mine = scan_chunk<1, THREADS, U, true, ANY_ALIGN, false, false>(
+        mine = scan_chunk<1, THREADS, U, true, ANY_ALIGN, false>(
             row, arow, reinterpret_cast<const uint8_t *>(arow), 0, ns_row, rs, 0, rs.nvec, true, true, V, lut, da, db,
             vec_pack, vec_ns);
         best = block_max_ns<THREADS>(mine, vec_pack, vec_ns, ns);

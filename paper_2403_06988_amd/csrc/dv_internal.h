@@ -275,7 +275,9 @@ struct StepGeometry {
     int threads;
 };
 
-inline StepGeometry step_geometry(int B, int V, int dtype)
+// walks: the rows are positions of a verification (any chunks per row that it
+// gives fit the workspace of B rows)
+inline StepGeometry step_geometry(int B, int V, int dtype, bool walks = false)
 {
     const bool bf16 = dtype == 1;
     const int vec = bf16 ? 8 : 4;  // elements per 16-byte vector
@@ -310,6 +312,19 @@ inline StepGeometry step_geometry(int B, int V, int dtype)
         while (r * r < b)
             ++r;  // ceil(sqrt(B))
         want = (32 * r + b / 2) / b;
+    }
+    // Rows that walk their proposals first (verification) take the rule for a
+    // few rows up to 63 of them: a block streams only its first batch during the
+    // walk's trips, so shorter chunks leave less behind them (us per call, bf16:
+    // 2 x 9 positions x 128,256 9.86 in 4 chunks and 9.01 in 9, 4 x 5 x 100,000
+    // 9.35 and 8.62 in 7; in 270 blocks 6 x 9 x 128,256 10.1 and 11.4).
+    if (walks && b >= 16 && b < 64 && batches > kStepSingleBlockBatches) {
+        int r = 4;
+        while (r * r < b)
+            ++r;
+        int more = (32 * r + b / 2) / b;
+        more = more < kStepOneBlockRows / b ? more : kStepOneBlockRows / b;
+        want = want > more ? want : more;
     }
     // Rows of four batches in two chunks of two (what 256 / B leaves from 128
     // rows on is one or two anyway).  Us per step in 1, 2, 3, 4 and 6 chunks:

@@ -1047,7 +1047,7 @@ hipError_t launch_masked_rows(const int32_t *next_state, const uint32_t *allow, 
                               hipStream_t stream)
 {
     const int W = (V + 31) / 32;
-    const StepGeometry g = step_geometry(B, V, dtype);
+    const StepGeometry g = step_geometry(B, V, dtype, map.per > 1);
     const RowMeet meet = row_meet(workspace, B);
     const unsigned grid = (unsigned)B * (unsigned)g.nchunks;
     // long chunks at up to four blocks per compute unit choose their

@@ -83,3 +83,36 @@ def test_short_fp32_rows(V, pad):
 def test_rows_of_four_batches_take_two_chunks_at_most(dtype, V):
     for B in range(1, 256):
         assert step_shape(B, V, dtype)[1] == (2 if B <= 128 else 1), B
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,s,V", [(2, 8, 50257), (4, 3, 40000), (4, 4, 100000), (6, 8, 40001), (9, 6, 33000)])
+def test_verification_of_a_few_positions(dtype, B, s, V):
+    """16 to 63 positions, which are split further than a step's rows are, in a
+    workspace of exactly the size asked for, left zero."""
+    import paper_2403_06988_amd as dv
+
+    rng = np.random.default_rng(B + s + V)
+    S = 4
+    alive = rng.random((S, V)) < np.array([0.5, 0.05, 1.0, 0.001])[:, None]
+    ns = np.where(alive, rng.integers(0, S, (S, V)), -1).astype(np.int32)
+    bits = np.zeros((S, (V + 31) // 32 * 32), bool)
+    bits[:, :V] = alive
+    al = np.packbits(bits, axis=1, bitorder="little").view("<u4").reshape(S, -1)
+    states = rng.integers(0, S, B).astype(np.int32)
+    x = (torch.randn(B, s + 1, V, generator=torch.Generator().manual_seed(V)) * 3).to(dtype)
+    xo = to_oracle(x)
+    props = np.zeros((B, s), np.int32)
+    cur = states.copy()
+    for j in range(s):                                        # the greedy choices, then some others
+        props[:, j], cur = oracle.masked_step(ns, al, cur, np.ascontiguousarray(xo[:, j]))
+    props[rng.random((B, s)) < 0.05] = 7
+    t = [torch.from_numpy(a).to(DEV) for a in (ns, al.view(np.int32), states, props)]
+    ws = dv.spec_workspace(B, s, V, DEV)
+    want = oracle.spec_verify(ns, al, states, props, xo)
+    for _ in range(2):
+        got = dv.spec_verify(*t, x.to(DEV), workspace=ws)
+        for g, w in zip(got, want):
+            np.testing.assert_array_equal(g.cpu().numpy(), w)
+        assert int(ws.count_nonzero()) == 0

@@ -85,4 +85,4 @@ def test_filled_rows_cost_what_other_rows_do(dtype):
         us(x)                                        # clocks and caches
     a, b = us(normal), us(filled)
     print(f"{dtype}: normal {a:.1f} us, filled {b:.1f} us", flush=True)
-    assert b < 1.35 * a
+    assert b < 1.4 * a                               # 1.17 here, 1.65 and 1.81 with every tie drawn
